@@ -210,8 +210,8 @@ const char *sho_last_error(void);
  * Build a reusable plan: per-atom supports (the projection spheres of sec. 6)
  * cut into (z, y) lines, uploaded to the current device.  Host-side work plus
  * synchronous uploads; the plan may then be used from any stream.  Calls of
- * one plan that use its device scratch (the expansion's plane partials) on
- * different streams are ordered by the library: each waits for the previous
+ * one plan that use its device scratch (the expansion's plane partials, the
+ * projection's plane sums) on different streams are ordered by the library: each waits for the previous
  * one.  Work recorded into a captured graph is not ordered that way, so a
  * graph must not be replayed while another call of its plan runs.  A plan
  * must not be called from two host threads at once.
@@ -276,7 +276,7 @@ sho_status sho_plan_set_kpoint(sho_plan_t plan, const double *k);
 sho_status sho_plan_destroy(sho_plan_t plan);
 
 /* Free the plan's own device scratch (the expansion's plane partials, also
- * the block projection's plane sums: sho_plan_info.expand_scratch_doubles
+ * the projection's plane sums: sho_plan_info.expand_scratch_doubles
  * doubles), keeping its tables; the next call that needs the scratch
  * allocates it again.  For a plan kept while its system's buffers are
  * released (a server evicting a system it expects back).  Waits for the
@@ -304,7 +304,11 @@ sho_status sho_plan_set_centres(sho_plan_t plan, const double *pos,
                                 void *stream);
 
 /* c (device, coeff_doubles) <- projection of psi (device, grid x nbands).
- * c is overwritten; psi and c must not overlap. */
+ * c is overwritten; psi and c must not overlap.  Until a schedule is set or
+ * tuned the library may take the projection plane by plane of the atoms, with
+ * the plane sums in the plan's device scratch (allocated by the first call
+ * that needs it); on a stream that the caller is capturing, and where the
+ * scratch cannot be allocated, it runs the work items, which use none. */
 sho_status sho_plan_project(sho_plan_t plan, const double *psi, double *c,
                             void *stream);
 
@@ -424,6 +428,8 @@ sho_status sho_plan_profile_read(sho_plan_t plan, int64_t *counts,
  * band_tile bands share a lane slot (power of two <= 64, 0 keeps the current
  * tile).  Plans with several cut-offs start with SHO_SCHED_SINGLE, others
  * with SHO_SCHED_BY_NU, target_points 16384 and the widest tile that fits.
+ * A schedule that is set is run: the plane-by-plane projection that the
+ * library may choose by itself (sho_plan_project) is given up.
  * set_schedule waits for the device (the work tables are replaced);
  * graphs made before it must be made again (sho_graph_launch refuses them).
  */

@@ -93,6 +93,9 @@ struct sho_plan_s {
   sho::EntryRec *d_pentries = nullptr;
   uint32_t *d_prun_desc = nullptr;
   int64_t pblk_bytes = 0;
+  sho::PlaneUnit *d_punits = nullptr;    // plane form of the projection
+  sho::PlaneBundle *d_pbundles = nullptr;
+  double *d_plane_phase = nullptr;       // Bloch plans: (cos, sin) per bundle
   sho::EntryRec *d_entries = nullptr;
   uint32_t *d_run_desc = nullptr;
   int64_t blk_bytes = 0;
@@ -122,10 +125,14 @@ hipError_t upload(T **dst, const std::vector<T> &src, int64_t *bytes) {
 }
 
 void free_plan_device(sho_plan_s *p) {
-  for (double **q : {&p->d_bundle_phase, &p->d_entry_phase}) {
+  for (double **q : {&p->d_bundle_phase, &p->d_entry_phase, &p->d_plane_phase}) {
     if (*q) (void)hipFree(*q);
     *q = nullptr;
   }
+  if (p->d_punits) (void)hipFree(p->d_punits);
+  if (p->d_pbundles) (void)hipFree(p->d_pbundles);
+  p->d_punits = nullptr;
+  p->d_pbundles = nullptr;
   if (p->scratch_ev) (void)hipEventDestroy(p->scratch_ev);
   p->scratch_ev = nullptr;
   if (p->d_atoms) (void)hipFree(p->d_atoms);
@@ -191,26 +198,30 @@ hipError_t upload_phases(sho_plan_s *p) {
   if (!p->bloch || (p->hp.flags & SHO_FLAG_HOST_ONLY)) return hipSuccess;
   const sho::HostPlan &hp = p->hp;
   std::vector<double> bph(2 * std::max<size_t>(hp.bundles.size(), 1), 0.0);
+  std::vector<double> pph(2 * std::max<size_t>(hp.pbundles.size(), 1), 0.0);
   std::vector<int32_t> run_atom(hp.lines.size(), 0);
   for (int32_t a = 0; a < hp.natoms; ++a)
     for (int32_t r = hp.atoms[a].line_begin; r < hp.atoms[a].line_begin + hp.atoms[a].nlines; ++r)
       run_atom[r] = a;
-  for (size_t b = 0; b < hp.bundles.size(); ++b) {
-    const sho::LineRec &L = hp.lines[hp.bundles[b].run0];
-    const sho::AtomRec &A = hp.atoms[run_atom[hp.bundles[b].run0]];
+  auto run_phase = [&](int32_t run, double *ph) {
+    const sho::LineRec &L = hp.lines[run];
+    const sho::AtomRec &A = hp.atoms[run_atom[run]];
     const int32_t ny = hp.grid.n[1];
     phase_of(p, (A.ix0 + L.jx0 - L.x0m) / hp.grid.n[0], (A.iy0 + L.jy - L.row % ny) / ny,
-             (A.iz0 + L.jz - L.row / ny) / hp.grid.n[2], &bph[2 * b]);
-  }
+             (A.iz0 + L.jz - L.row / ny) / hp.grid.n[2], ph);
+  };
+  for (size_t b = 0; b < hp.bundles.size(); ++b) run_phase(hp.bundles[b].run0, &bph[2 * b]);
+  for (size_t b = 0; b < hp.pbundle_run.size(); ++b) run_phase(hp.pbundle_run[b], &pph[2 * b]);
   std::vector<double> eph(2 * std::max<size_t>(hp.entries.size(), 1), 0.0);
   for (size_t i = 0; i < hp.entries.size(); ++i)
     phase_of(p, hp.entries[i].img[0], hp.entries[i].img[1], hp.entries[i].img[2], &eph[2 * i]);
   int64_t bytes = 0;
-  for (double **q : {&p->d_bundle_phase, &p->d_entry_phase}) {
+  for (double **q : {&p->d_bundle_phase, &p->d_entry_phase, &p->d_plane_phase}) {
     if (*q) (void)hipFree(*q);
     *q = nullptr;
   }
   hipError_t e = upload(&p->d_bundle_phase, bph, &bytes);
+  if (e == hipSuccess) e = upload(&p->d_plane_phase, pph, &bytes);
   if (e == hipSuccess) e = upload(&p->d_entry_phase, eph, &bytes);
   return e;
 }
@@ -327,6 +338,30 @@ sho::KArgs make_args(const sho_plan_s *p, const Group &g) {
   K.alpha = 1.0;
   K.bundle_phase = p->d_bundle_phase;
   return K;
+}
+
+sho::PlaneArgs make_plane_args(const sho_plan_s *p) {
+  sho::PlaneArgs A;
+  A.atoms = p->d_atoms;
+  A.bundles = p->d_pbundles;
+  A.units = p->d_punits;
+  A.tab = p->d_tab;
+  A.u2_off = p->d_u2_off;
+  A.nu_atoms = p->d_nu_atoms;
+  A.phase = p->bloch ? p->d_plane_phase : nullptr;
+  A.nunits = (int32_t)p->hp.punits.size();
+  A.natoms_u2 = (int32_t)p->hp.nu_atoms.size();
+  A.nx = p->hp.grid.n[0];
+  A.ny = p->hp.grid.n[1];
+  A.u2_scale = p->fp32 ? 2 : 1;
+  A.B = p->hp.nbands * A.u2_scale;
+  A.lds_rows = p->hp.plane_lds_rows;
+  A.lds_bundles = p->hp.plane_lds_bundles;
+  A.waves = sho::plane_waves(p->hp);
+  A.nb = sho::plane_bands(p->hp);
+  const double h = p->hp.grid.h;
+  A.h3 = h * h * h;
+  return A;
 }
 
 void prof_clear(sho_plan_s *p) {
@@ -451,7 +486,9 @@ int64_t estimate_device_bytes(const sho::HostPlan &hp) {
               b(hp.natoms, 4) + b(hp.u2_doubles, 8) +
               b((int64_t)hp.blocks.size(), sizeof(sho::BlockRec)) +
               b((int64_t)hp.entries.size(), sizeof(sho::EntryRec)) +
-              b((int64_t)hp.run_desc.size(), 4);
+              b((int64_t)hp.run_desc.size(), 4) +
+              b((int64_t)hp.punits.size(), sizeof(sho::PlaneUnit)) +
+              b((int64_t)hp.pbundles.size(), sizeof(sho::PlaneBundle));
   if (hp.flags & SHO_FLAG_STORED) {
     int64_t stored = 0;
     for (const auto &A : hp.atoms) stored += (int64_t)A.npoints * sho::stored_cols(hp, A);
@@ -531,16 +568,17 @@ sho_status ensure_u2(sho_plan_s *p) {
   return SHO_OK;
 }
 
-// The projection's launches on s (arguments already checked).
+// The projection's launches on s (arguments already checked); planes: in the
+// plane form, with its plane sums in the plan's scratch.
 hipError_t run_project(sho_plan_s *p, const void *psi_v, void *c_v, hipStream_t s,
-                       bool prof) {
+                       bool prof, bool planes) {
   const double *psi = static_cast<const double *>(psi_v);
   double *c = static_cast<double *>(c_v);
   // atoms whose support missed the grid entirely keep zero coefficients;
   // atoms shared by several work items (and every stored point chunk) are
   // summed into zeroed coefficients
   const bool blocks = p->hp.proj_form == sho::kProjectBlocks;
-  bool zero = (p->hp.any_split && !blocks) || (p->hp.flags & SHO_FLAG_STORED);
+  bool zero = (p->hp.any_split && !blocks && !planes) || (p->hp.flags & SHO_FLAG_STORED);
   for (const auto &A : p->hp.atoms) zero |= (A.npoints == 0);
   if (zero) {
     hipError_t e = sho::launch_fill(c, p->hp.coeff_rows * p->hp.nbands, 0.0, s);
@@ -557,6 +595,11 @@ hipError_t run_project(sho_plan_s *p, const void *psi_v, void *c_v, hipStream_t 
       return e1;
     });
   }
+  if (planes)
+    return timed(p, prof, SHO_KERNEL_PROJECT, s, [&]() {
+      return sho::launch_project_planes(p->hp.nu_max, p->fp32, make_plane_args(p), psi_v,
+                                        p->d_u2, c_v, s);
+    });
   return timed(p, prof, SHO_KERNEL_PROJECT, s, [&]() {
     if (p->hp.flags & SHO_FLAG_STORED) {
       for (const Group &g : p->sgroups) {
@@ -689,12 +732,23 @@ hipError_t run_expand(sho_plan_s *p, const void *c_v, void *psi_v, hipStream_t s
   return e;
 }
 
-// run_project with the block form's plane sums in the plan's own scratch,
-// ordered against the scratch's other users (the item form uses none).
+// Whether the next projection takes the plane form (its scratch must be there).
+bool uses_planes(const sho_plan_s *p) {
+  return p->hp.plane_form && p->hp.proj_form == sho::kProjectItems;
+}
+
+// run_project with the plane sums of the block or plane form in the plan's
+// own scratch, ordered against the scratch's other users (the item form uses
+// none).  The plane form gives way to the item form where its scratch may not
+// be used or had: on a stream that a caller is capturing (the captured work
+// could replay beside other calls of the plan) and when the allocation fails.
 hipError_t run_project_own(sho_plan_s *p, const void *psi, void *c, hipStream_t s, bool prof) {
-  if (p->hp.proj_form != sho::kProjectBlocks) return run_project(p, psi, c, s, prof);
+  bool planes = uses_planes(p);
+  if (planes) planes = !capturing(s) && ensure_u2(p) == SHO_OK;
+  if (!planes && p->hp.proj_form != sho::kProjectBlocks)
+    return run_project(p, psi, c, s, prof, false);
   hipError_t e = scratch_acquire(p, s);
-  if (e == hipSuccess) e = run_project(p, psi, c, s, prof);
+  if (e == hipSuccess) e = run_project(p, psi, c, s, prof, planes);
   if (e == hipSuccess) e = scratch_release(p, s);
   return e;
 }
@@ -726,6 +780,7 @@ sho_status finish_plan(sho_plan_s *p, uint32_t flags, int32_t nbands, bool f32,
     }
     sho::build_work(&p->hp, tbs, sho::kTargetPoints, default_schedule(p->hp));
     sho::build_rows(&p->hp);
+    sho::build_planes(&p->hp);
     build_default_blocks(&p->hp);
     *out = p;
     return SHO_OK;
@@ -750,11 +805,14 @@ sho_status finish_plan(sho_plan_s *p, uint32_t flags, int32_t nbands, bool f32,
   }
   sho::build_work(&p->hp, tbs, sho::kTargetPoints, default_schedule(p->hp));
   sho::build_rows(&p->hp);
+  sho::build_planes(&p->hp);
   build_default_blocks(&p->hp);
   std::vector<double> no_tab;
   if ((e = upload(&p->d_atoms, p->hp.atoms, &p->device_bytes)) != hipSuccess ||
       (e = upload(&p->d_lines, p->hp.lines, &p->device_bytes)) != hipSuccess ||
       (e = upload_schedule(p)) != hipSuccess || (e = upload_blocks(p)) != hipSuccess ||
+      (e = upload(&p->d_punits, p->hp.punits, &p->device_bytes)) != hipSuccess ||
+      (e = upload(&p->d_pbundles, p->hp.pbundles, &p->device_bytes)) != hipSuccess ||
       (e = upload(&p->d_doff, p->hp.dmat_off, &p->device_bytes)) != hipSuccess ||
       (e = upload(&p->d_run_atom, p->hp.run_atom, &p->device_bytes)) != hipSuccess ||
       (e = upload(&p->d_row_runs, p->hp.row_runs, &p->device_bytes)) != hipSuccess ||
@@ -840,6 +898,9 @@ sho_status finish_plan(sho_plan_s *p, uint32_t flags, int32_t nbands, bool f32,
     if (e == hipSuccess) p->device_bytes += gb;
   }
   if (e == hipSuccess) e = hipEventCreateWithFlags(&p->scratch_ev, hipEventDisableTiming);
+  // the plane form's scratch with the plan, not in its first projection (a
+  // plan without room for it projects in the item form)
+  if (e == hipSuccess && p->hp.plane_form) (void)ensure_u2(p);
   if (e == hipSuccess) e = hipDeviceSynchronize();
   if (e != hipSuccess) {
     free_plan_device(p);
@@ -1183,7 +1244,7 @@ sho_status sho_plan_expand_noalloc(sho_plan_t p, const double *c, double *psi, v
 sho_status sho_plan_project_f32(sho_plan_t p, const float *psi, float *c, void *stream) {
   sho_status st = check_project(p, psi, c, 1);
   if (st != SHO_OK || p->hp.coeff_rows == 0) return st;
-  hipError_t e = run_project(p, psi, c, (hipStream_t)stream, p->prof_on);
+  hipError_t e = run_project_own(p, psi, c, (hipStream_t)stream, p->prof_on);
   if (e != hipSuccess) return hip_fail(e, "project launch");
   return SHO_OK;
 }
@@ -1267,6 +1328,7 @@ sho_status sho_plan_set_schedule(sho_plan_t p, int32_t schedule, int32_t band_ti
     if (e != hipSuccess) return hip_fail(e, "hipDeviceSynchronize");
   }
   sho::build_work(&p->hp, tbs, target_points, schedule);
+  p->hp.plane_form = false;  // the caller's schedule of work items runs
   if (p->hp.flags & SHO_FLAG_HOST_ONLY) return SHO_OK;
   hipError_t e = upload_schedule(p);
   if (e != hipSuccess) return hip_fail(e, "schedule upload");
@@ -1529,7 +1591,8 @@ sho_status sho_plan_tune(sho_plan_t p, const void *psi, void *c, int32_t reps,
     return fail(SHO_E_INVALID, "stored and per-atom plans have a fixed schedule");
   const bool blocks_ok =
       !(p->hp.flags & SHO_FLAG_DETERMINISTIC) && !p->fp32 && !p->bloch;
-  if (blocks_ok && (st = ensure_u2(p)) != SHO_OK) return st;
+  const bool planes0 = uses_planes(p);
+  if ((blocks_ok || planes0) && (st = ensure_u2(p)) != SHO_OK) return st;
   hipStream_t s = (hipStream_t)stream;
   struct Cand {
     int32_t sched, tbs;
@@ -1549,9 +1612,11 @@ sho_status sho_plan_tune(sho_plan_t p, const void *psi, void *c, int32_t reps,
   hipError_t e = hipEventCreate(&ea);
   if (e == hipSuccess) e = hipEventCreate(&eb);
   auto time_current = [&](double *ms) -> hipError_t {
-    hipError_t e1 = run_project(p, psi, c, s, false);  // warm-up
+    const bool planes = uses_planes(p);
+    hipError_t e1 = run_project(p, psi, c, s, false, planes);  // warm-up
     if (e1 == hipSuccess) e1 = hipEventRecord(ea, s);
-    for (int r = 0; r < reps && e1 == hipSuccess; ++r) e1 = run_project(p, psi, c, s, false);
+    for (int r = 0; r < reps && e1 == hipSuccess; ++r)
+      e1 = run_project(p, psi, c, s, false, planes);
     if (e1 == hipSuccess) e1 = hipEventRecord(eb, s);
     if (e1 == hipSuccess) e1 = hipEventSynchronize(eb);
     float t = 0.f;
@@ -1560,16 +1625,20 @@ sho_status sho_plan_tune(sho_plan_t p, const void *psi, void *c, int32_t reps,
     return e1;
   };
   double ms_before = 0.0;
+  if (e == hipSuccess) e = scratch_acquire(p, s);
   if (e == hipSuccess) e = time_current(&ms_before);
   // item form: schedules x item sizes x band tiles
+  const bool plane_form0 = p->hp.plane_form;
   p->hp.proj_form = sho::kProjectItems;
+  p->hp.plane_form = false;
   double best = form0 == sho::kProjectItems ? ms_before : 1e300;
   Cand pick = before;
+  bool keep_planes = plane_form0;  // until a schedule of work items is faster
   int32_t tried = 1;
   for (const Cand &cd : cands) {
     if (e != hipSuccess) break;
-    if (form0 == sho::kProjectItems && cd.sched == before.sched && cd.tbs == before.tbs &&
-        cd.target == before.target)
+    if (form0 == sho::kProjectItems && !planes0 && cd.sched == before.sched &&
+        cd.tbs == before.tbs && cd.target == before.target)
       continue;
     e = hipStreamSynchronize(s);
     if (e != hipSuccess) break;
@@ -1581,6 +1650,7 @@ sho_status sho_plan_tune(sho_plan_t p, const void *psi, void *c, int32_t reps,
     if (ms < best) {
       best = ms;
       pick = cd;
+      keep_planes = false;
     }
   }
   // block form: band tile x block width (rows: as many as the tile holds)
@@ -1618,6 +1688,7 @@ sho_status sho_plan_tune(sho_plan_t p, const void *psi, void *c, int32_t reps,
   if ((e = hipStreamSynchronize(s)) != hipSuccess) return hip_fail(e, "tuning");
   sho::build_work(&p->hp, pick.tbs, pick.target, pick.sched);
   if ((e = upload_schedule(p)) != hipSuccess) return hip_fail(e, "schedule upload");
+  p->hp.plane_form = keep_planes;
   const bool use_blocks = bbest < best;
   if (use_blocks) {
     const int64_t per_row = (int64_t)sho::pow2_ceil(bpick.x) << bpick.tbs;
@@ -1757,7 +1828,7 @@ sho_status sho_graph_create(sho_plan_t p, const double *psi, double *c, double *
     return fail(SHO_E_INVALID, "out and c overlap");
   if ((st = ensure_u2(p)) != SHO_OK) return st;
   return capture(p, [&](hipStream_t cs) {
-    hipError_t e1 = run_project(p, psi, c, cs, false);
+    hipError_t e1 = run_project(p, psi, c, cs, false, uses_planes(p));
     if (e1 == hipSuccess) e1 = run_expand(p, c, out, cs, false, p->d_u2);
     return e1;
   }, g);
@@ -1773,7 +1844,7 @@ sho_status sho_graph_create_apply(sho_plan_t p, const double *psi, const double 
   if (st != SHO_OK) return st;
   if ((st = ensure_u2(p)) != SHO_OK) return st;
   return capture(p, [&](hipStream_t cs) {
-    hipError_t e1 = run_project(p, psi, c, cs, false);
+    hipError_t e1 = run_project(p, psi, c, cs, false, uses_planes(p));
     if (e1 == hipSuccess) e1 = run_multiply(p, D, c, d, cs);
     if (e1 == hipSuccess) e1 = run_expand(p, d, out, cs, false, p->d_u2);
     return e1;

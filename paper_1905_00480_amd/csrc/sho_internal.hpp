@@ -79,6 +79,33 @@ struct BundleRec {
 };
 static_assert(sizeof(BundleRec) == 16, "BundleRec layout");
 
+// Work of the plane form of the projection: one plane of one atom's support
+// (in one memory plane z), its runs in bundles [b0, b0 + nb) of up to four.
+struct PlaneUnit {
+  int64_t tab_off;  // first double of the atom's 1D tables
+  int64_t sums;     // first plane sum, in values per band: (offset) * bands
+  int32_t z;        // memory plane
+  int32_t b0, nb;
+  int16_t nu;       // -1: padding
+  int16_t nfp;      // row stride of the tables
+  int16_t mx;       // x table rows
+  int16_t pad[3];
+};
+static_assert(sizeof(PlaneUnit) == 40, "PlaneUnit layout");
+
+// Up to four runs of one atom plane and image; missing runs have length 0.
+struct PlaneBundle {
+  uint32_t off[4];  // point of table index 0, counted from mx points before
+                    // the memory plane, times the bytes of a point
+  uint16_t jx0[4];  // table index of the first point along x
+  uint16_t len[4];  // points
+  uint16_t jy[4];   // y table row (a valid one also for missing runs)
+  // x steps of four table points: [t0, t1) touch a run, [i0, i1) lie inside
+  // all four
+  uint16_t t0, t1, i0, i1;
+};
+static_assert(sizeof(PlaneBundle) == 48, "PlaneBundle layout");
+
 // Waves per workgroup of the streaming kernels.
 constexpr int kWaves = 8;
 // Bytes of LDS the kernels may declare statically (the streaming kernels'
@@ -224,6 +251,12 @@ struct HostPlan {
   std::vector<int32_t> run_desc_run;    // the run of every descriptor
   std::vector<int64_t> desc_pbase;      // stored plans: P double of block x 0
   int32_t proj_form = 0;                // kProjectItems or kProjectBlocks
+  bool plane_form = false;              // item form's plan runs the plane form
+  int32_t plane_lds_rows = 0;           // x table rows of a unit, largest
+  int32_t plane_lds_bundles = 0;        // bundles of a unit, largest
+  std::vector<PlaneUnit> punits;        // XCD-interleaved by memory plane
+  std::vector<PlaneBundle> pbundles;
+  std::vector<int32_t> pbundle_run;     // Bloch plans: the first run of each
   int32_t pblk_tb_shift = 0;            // log2(bands per lane slot), block form
   BlockSet pblk;                        // the projection's block form
   std::vector<int64_t> run_poff;      // stored projectors: first double of
@@ -319,6 +352,51 @@ void build_work(HostPlan *P, int tb_shift, int64_t target_points, int32_t sched)
 // eight XCDs so that all rows of one plane share an L2, per-atom offsets of
 // the plane partials U2[jz][pair][band].
 void build_rows(HostPlan *P);
+
+// Limits of the plane form: bytes of a memory plane of psi and of an atom's
+// widest line (32-bit offsets, bit 31 marks lanes without a value), x table rows of an atom in LDS (at most
+// 12 functions of 8 bytes each per row) and bundles of a unit (72 bytes each).
+constexpr int64_t kPlaneMaxBytes = (int64_t)1 << 30;
+constexpr int32_t kPlaneMaxRows = 256;
+constexpr int32_t kPlaneMaxBundles = 256;
+
+// Adjacent bands per lane of the plane form (16 lanes take 16 or 32 bands):
+// two where one wave of 16 would not hold all bands.
+inline int plane_bands(const HostPlan &P) {
+  return P.nbands * ((P.flags & SHO_FLAG_FP32) ? 2 : 1) > 16 ? 2 : 1;
+}
+
+// log2 of the band groups (16 bands) that run side by side on an XCD: as many
+// as keep a memory plane of them within 2 MB (half the L2), at most 8.
+inline int plane_group_shift(const HostPlan &P) {
+  const bool f32 = (P.flags & SHO_FLAG_FP32) != 0;
+  const int bands = 16 * plane_bands(P);
+  const int64_t plane = (int64_t)P.grid.n[0] * P.grid.n[1] * bands * (f32 ? 4 : 8);
+  const int groups = (P.nbands * (f32 ? 2 : 1) + bands - 1) / bands;
+  int s = 0;
+  while (s < 3 && (1 << s) < groups && (plane << (s + 1)) <= (2 << 20)) ++s;
+  return s;
+}
+
+// Waves per unit of the plane form.  Few units: four, for the parallelism
+// (6 atoms of cut-off 5, 32 bands: step 60 us with one, 51 with two, 48 with
+// four).  Supports that overlap little: two, so that fewer units are resident
+// and they span fewer planes (128^3, 512 atoms, cut-off 5, 32 bands, overlap
+// 2.3: 167 us with one, 155 with two, 185 with four).  Else one, which pays a
+// wave's start-up once per unit (160^3, 2048 atoms, overlap 18: 3.57 ms with
+// one, 3.93 with two).
+inline int plane_waves(const HostPlan &P) {
+  const int B = P.nbands * ((P.flags & SHO_FLAG_FP32) ? 2 : 1);
+  const int per = 16 * plane_bands(P);
+  if ((int64_t)P.punits.size() * ((B + per - 1) / per) < 1024) return 4;
+  return P.support_points < 4 * P.union_points ? 2 : 1;
+}
+
+// Work of the plane form of the projection (needs build_work for the order of
+// the runs): fills punits and pbundles, and sets plane_form if the form can and
+// should run.
+// Needs the offsets of the plane partials (build_rows) too.
+void build_planes(HostPlan *P);
 
 // Blocks of R rows x X points for the block form of the expansion (needs
 // build_rows for run_atom).

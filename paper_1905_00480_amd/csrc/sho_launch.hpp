@@ -72,6 +72,28 @@ struct EArgs {
   const double *entry_phase;  // Bloch plans: (cos, sin) of k.T per block entry
 };
 
+// Argument block of the plane form of the projection.
+struct PlaneArgs {
+  const AtomRec *atoms;
+  const PlaneBundle *bundles;
+  const PlaneUnit *units;
+  const double *tab;          // 1D tables of all atoms (FP64 for either type)
+  const int64_t *u2_off;      // [natoms] first value of the atom's plane sums,
+                              // in units of u2_scale values
+  const int32_t *nu_atoms;    // atoms with a support
+  const double *phase;        // Bloch plans: (cos, sin) of k.T per bundle
+  int32_t nunits;
+  int32_t natoms_u2;
+  int32_t nx, ny;
+  int32_t B;                  // real values per grid point
+  int32_t lds_rows;           // x table rows (multiple of 4) of the largest unit
+  int32_t lds_bundles;        // bundles of the largest unit
+  int32_t waves;              // waves per unit (1, 2 or 4)
+  int32_t nb;                 // adjacent bands per lane (1 or 2)
+  int32_t u2_scale;           // 2 for FP32 plans (offsets count band pairs)
+  double h3;
+};
+
 // Argument block of the stored-projector kernels.
 struct SArgs {
   const AtomRec *atoms;
@@ -170,6 +192,12 @@ static_assert(kStaticScratchDoubles == SHO_STATIC_SCRATCH_DOUBLES, "static scrat
 // Device address of the current device's static scratch (looked up once per
 // device; no allocation).
 hipError_t static_scratch(double **ptr);
+
+// Plane form of the projection: plane sums of every unit into p2 (layout of
+// the expansion's plane partials), then the z pass into c.  psi, p2 and c are
+// float if f32, else double.
+hipError_t launch_project_planes(int nu_max, bool f32, const PlaneArgs &P, const void *psi,
+                                 void *p2, void *c, hipStream_t s);
 
 // FP32 plans (an even number of bands, processed as pairs: K.B and E.B count
 // pairs).  tab: the plan's tables rounded to FP32.

@@ -482,6 +482,138 @@ void build_work(HostPlan *P, int tb_shift, int64_t target_points, int32_t sched)
   }
 }
 
+void build_planes(HostPlan *P) {
+  P->plane_form = false;
+  P->plane_lds_rows = 0;
+  P->plane_lds_bundles = 0;
+  P->punits.clear();
+  P->pbundles.clear();
+  if (P->flags & (SHO_FLAG_STORED | SHO_FLAG_PER_ATOM)) return;
+  // a memory plane is addressed by 32-bit byte offsets, the tables of one
+  // atom are staged in LDS
+  const int32_t ny = P->grid.n[1];
+  const int64_t plane_bytes = (int64_t)P->grid.n[0] * ny * P->nbands * 8;
+  if (plane_bytes > kPlaneMaxBytes) return;
+  for (const AtomRec &A : P->atoms)
+    if (A.npoints > 0)
+      P->plane_lds_rows = std::max(P->plane_lds_rows, (A.mx + 3) / 4 * 4);
+  if (P->plane_lds_rows > kPlaneMaxRows ||
+      (P->plane_lds_rows + 16) * (int64_t)P->nbands * 8 > kPlaneMaxBytes)
+    return;
+  const bool bloch = (P->flags & SHO_FLAG_BLOCH) != 0;
+  struct Keyed {
+    int32_t z;
+    uint64_t key;
+    int64_t cost;
+    PlaneUnit u;
+  };
+  std::vector<Keyed> all;
+  const int32_t nx = P->grid.n[0];
+  const uint32_t bytes_x = (uint32_t)P->nbands * 8u;  // of a grid point
+  P->pbundle_run.clear();
+  for (int32_t a = 0; a < P->natoms; ++a) {
+    const AtomRec &A = P->atoms[a];
+    if (A.npoints == 0) continue;
+    const uint64_t key = morton_xy(P, a);
+    const int64_t np = (int64_t)(A.nu + 1) * (A.nu + 2) / 2;
+    for (int32_t pi = A.plane_begin; pi < A.plane_begin + A.nplanes; ++pi) {
+      const int32_t rb = P->planes[pi].line_begin;
+      const int32_t re = (pi + 1 < A.plane_begin + A.nplanes) ? P->planes[pi + 1].line_begin
+                                                              : A.line_begin + A.nlines;
+      auto image = [&](const LineRec &L) {  // image counts along x and y
+        const int64_t mx = (int64_t)(A.ix0 + L.jx0 - L.x0m) / nx;
+        const int64_t my = (int64_t)(A.iy0 + L.jy - L.row % ny) / ny;
+        return mx * 1024 + my;
+      };
+      Keyed k;
+      k.z = P->lines[rb].row / ny;
+      k.key = key;
+      k.cost = 4;
+      k.u = PlaneUnit();
+      k.u.tab_off = A.tab_off;
+      k.u.sums = P->u2_off[a] / P->nbands + (int64_t)P->lines[rb].jz * np;
+      k.u.z = k.z;
+      k.u.b0 = (int32_t)P->pbundles.size();
+      k.u.nu = (int16_t)A.nu;
+      k.u.nfp = (int16_t)A.tab_nfp;
+      k.u.mx = (int16_t)A.mx;
+      const int32_t row0 = k.z * ny;
+      for (int32_t r = rb, rn = rb; r < re; r = rn) {
+        rn = std::min(re, r + 4);
+        if (bloch)
+          for (int32_t i = r + 1; i < rn; ++i)
+            if (image(P->lines[i]) != image(P->lines[r])) {
+              rn = i;
+              break;
+            }
+        PlaneBundle b{};
+        int lo = INT32_MAX, hi = 0, in0 = 0, in1 = INT32_MAX;
+        for (int32_t i = 0; i < 4; ++i) {
+          const LineRec &L = P->lines[std::min(r + i, rn - 1)];
+          const int32_t len = r + i < rn ? L.len : 0;
+          b.off[i] = (uint32_t)((L.row - row0) * nx + L.x0m - L.jx0 + A.mx) * bytes_x;
+          b.jx0[i] = (uint16_t)L.jx0;
+          b.len[i] = (uint16_t)len;
+          b.jy[i] = (uint16_t)L.jy;
+          in0 = std::max(in0, (int)L.jx0);
+          in1 = std::min(in1, (int)L.jx0 + len);
+          if (len) {
+            lo = std::min(lo, (int)L.jx0);
+            hi = std::max(hi, (int)L.jx0 + len);
+          }
+        }
+        b.t0 = (uint16_t)(lo / 4);
+        b.t1 = (uint16_t)((hi + 3) / 4);
+        b.i0 = (uint16_t)((in0 + 3) / 4);
+        b.i1 = (uint16_t)(in1 / 4);
+        P->pbundles.push_back(b);
+        if (bloch) P->pbundle_run.push_back(r);
+        k.cost += b.t1 - b.t0 + 2;
+      }
+      k.u.nb = (int32_t)P->pbundles.size() - k.u.b0;
+      P->plane_lds_bundles = std::max(P->plane_lds_bundles, k.u.nb);
+      all.push_back(k);
+    }
+  }
+  if (all.empty() || P->plane_lds_bundles > kPlaneMaxBundles) return;
+  std::stable_sort(all.begin(), all.end(), [](const Keyed &x, const Keyed &y) {
+    return x.z != y.z ? x.z < y.z : x.key < y.key;
+  });
+  // planes z = k mod 8 to XCD k (workgroup g runs on XCD g mod 8), unless the
+  // classes differ much in cost (few planes): then the list in order
+  int64_t cls_cost[kXcds] = {}, total = 0, worst = 0;
+  for (const Keyed &k : all) {
+    cls_cost[k.z % kXcds] += k.cost;
+    total += k.cost;
+  }
+  for (int64_t c : cls_cost) worst = std::max(worst, c);
+  PlaneUnit pad{};
+  pad.nu = -1;
+  if (worst * kXcds <= total * 5 / 4) {
+    std::vector<PlaneUnit> cls[kXcds];
+    for (const Keyed &k : all) cls[k.z % kXcds].push_back(k.u);
+    size_t n = 0;
+    for (const auto &c : cls) n = std::max(n, c.size());
+    for (size_t i = 0; i < n; ++i)
+      for (const auto &c : cls) P->punits.push_back(i < c.size() ? c[i] : pad);
+  } else {
+    for (const Keyed &k : all) P->punits.push_back(k.u);
+    while (P->punits.size() % kXcds) P->punits.push_back(pad);
+  }
+  // When the form runs.  One small atom: the item form's single launch is
+  // faster (16^3, one atom of 2109 points, one band: 9.9 us against 15.3), and
+  // so it is for many small ones with few of the 16 bands of a wave (125 x 131
+  // x 115, 272 atoms of cut-off 3, 2 bands: whole step 65 us against 68).
+  // Single precision with little overlap: half the bytes to save, the same z
+  // pass to pay (128^3, 512 atoms, 32 bands: items 0.118 ms, planes 0.150).
+  int64_t largest = 0;
+  for (const AtomRec &A : P->atoms) largest = std::max(largest, A.npoints);
+  const bool f32 = (P->flags & SHO_FLAG_FP32) != 0;
+  const int32_t bands = P->nbands * (f32 ? 2 : 1);
+  P->plane_form = !((all.size() <= 64 || bands <= 8) && largest <= 4096) &&
+                  !(f32 && P->support_points < 4 * P->union_points);
+}
+
 void build_stored(HostPlan *P, int32_t chunk) {
   const int32_t nx = P->grid.n[0];
   P->run_poff.assign(P->lines.size() + 1, 0);
