@@ -120,8 +120,9 @@ typedef int32_t sho_status;
                                              derivative keep one coefficient
                                              tile per wave, added in wave
                                              order, and one work item per
-                                             atom; the expansion takes the
-                                             owner form (SHO_EXPAND_OWNER).
+                                             atom; the expansion runs as
+                                             tiles or in the owner form
+                                             (SHO_EXPAND_OWNER), both ordered.
                                              Repeated calls on the same inputs
                                              give identical bits.  FP64 only;
                                              not with SHO_FLAG_STORED,
@@ -193,10 +194,11 @@ typedef struct sho_plan_info {
   int64_t stored_bytes;    /* of which stored projector tables */
   int64_t union_points;    /* distinct grid points covered by any support */
   int64_t expand_points;   /* grid points the expansion reads and writes:
-                              the blocks (block form) or whole rows (row
-                              form) that some support touches */
+                              the tiles, the blocks (block form) or whole
+                              rows (row form) that some support touches */
   int64_t expand_scratch_doubles; /* plane partials of the expansion */
-  int64_t expand_blocks;   /* workgroup blocks of the block-form expansion */
+  int64_t expand_blocks;   /* workgroup blocks of the block-form expansion,
+                              or its tiles where it runs as tiles */
   int64_t expand_entries;  /* (atom plane, block) pairs of that form */
 } sho_plan_info;
 
@@ -478,7 +480,10 @@ sho_status sho_plan_get_project(sho_plan_t plan, int32_t *form, int32_t *block_r
  *              atomics, so the result is bitwise reproducible (the form of
  *              SHO_FLAG_DETERMINISTIC plans, which accept no other).
  * All read and write every touched value of psi once with plain loads and
- * stores.  For SHO_FLAG_STORED plans the forms are: 0 the atom-owner form
+ * stores.  The default of mode 1 (2 for deterministic plans) without a shape
+ * runs as tiles of 16 rows x 16 points whose sums stay in registers, in the
+ * plan's order and without atomics, wherever that was measured to be faster;
+ * a shape, or a band tile, picks the named form itself.  For SHO_FLAG_STORED plans the forms are: 0 the atom-owner form
  * (global atomics, default for nu_max > 2), 1 the block form with the
  * products on matrix cores (default for nu_max <= 2).  block_rows = block_x = 0 picks the default shape; a shape whose
  * tile (rows x points x bands per tile: 8, 16, 32 or 64, the power of two

@@ -9,6 +9,7 @@ Objects:
   sho_kernels.hip  gfx950 kernels
   sho_kernels_f32.hip  single-precision projection and expansion kernels
   sho_planes.hip   plane form of the projection (matrix cores)
+  sho_tiles.hip    tile form of the expansion (matrix cores)
 """
 import os
 import shutil
@@ -68,7 +69,7 @@ def build(verbose: bool = False, jobs: int = 3, sanitize: bool = False) -> str:
         objs.append(o)
     san_host = [f for x in SAN for f in ("-Xarch_host", x)] if sanitize else []
     for src in ("sho_api.cpp", "sho_server.cpp", "sho_kernels.hip", "sho_kernels_f32.hip",
-                "sho_planes.hip"):
+                "sho_planes.hip", "sho_tiles.hip"):
         o = os.path.join(bdir, src.rsplit(".", 1)[0] + ".o")
         lang = ["-x", "hip"] if src.endswith(".hip") else []
         cmd = [HIPCC] + HIP_FLAGS + san_host + lang + ["-c", os.path.join(CSRC, src), "-o", o]

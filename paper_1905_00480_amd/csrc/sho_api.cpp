@@ -93,6 +93,9 @@ struct sho_plan_s {
   sho::EntryRec *d_pentries = nullptr;
   uint32_t *d_prun_desc = nullptr;
   int64_t pblk_bytes = 0;
+  sho::BlockRec *d_tblocks = nullptr;    // tile form of the expansion
+  sho::TileEntry *d_tentries = nullptr;
+  double *d_tile_phase = nullptr;        // Bloch plans: (cos, sin) per entry
   sho::PlaneUnit *d_punits = nullptr;    // plane form of the projection
   sho::PlaneBundle *d_pbundles = nullptr;
   double *d_plane_phase = nullptr;       // Bloch plans: (cos, sin) per bundle
@@ -125,10 +128,15 @@ hipError_t upload(T **dst, const std::vector<T> &src, int64_t *bytes) {
 }
 
 void free_plan_device(sho_plan_s *p) {
-  for (double **q : {&p->d_bundle_phase, &p->d_entry_phase, &p->d_plane_phase}) {
+  for (double **q :
+       {&p->d_bundle_phase, &p->d_entry_phase, &p->d_plane_phase, &p->d_tile_phase}) {
     if (*q) (void)hipFree(*q);
     *q = nullptr;
   }
+  if (p->d_tblocks) (void)hipFree(p->d_tblocks);
+  if (p->d_tentries) (void)hipFree(p->d_tentries);
+  p->d_tblocks = nullptr;
+  p->d_tentries = nullptr;
   if (p->d_punits) (void)hipFree(p->d_punits);
   if (p->d_pbundles) (void)hipFree(p->d_pbundles);
   p->d_punits = nullptr;
@@ -146,7 +154,7 @@ void free_plan_device(sho_plan_s *p) {
     if (*q) (void)hipFree(*q);
     *q = nullptr;
   }
-  if (p->d_tab) (void)hipFree(p->d_tab);
+  if (p->d_tab) (void)hipFree(p->d_tab - sho::kTabPad);
   if (p->d_tab32) (void)hipFree(p->d_tab32);
   p->d_tab32 = nullptr;
   for (void *q : {(void *)p->d_run_atom, (void *)p->d_row_runs, (void *)p->d_rows,
@@ -215,13 +223,18 @@ hipError_t upload_phases(sho_plan_s *p) {
   std::vector<double> eph(2 * std::max<size_t>(hp.entries.size(), 1), 0.0);
   for (size_t i = 0; i < hp.entries.size(); ++i)
     phase_of(p, hp.entries[i].img[0], hp.entries[i].img[1], hp.entries[i].img[2], &eph[2 * i]);
+  std::vector<double> tph(2 * std::max<size_t>(hp.timages.size(), 1), 0.0);
+  for (size_t i = 0; i < hp.timages.size(); ++i)
+    phase_of(p, hp.timages[i][0], hp.timages[i][1], hp.timages[i][2], &tph[2 * i]);
   int64_t bytes = 0;
-  for (double **q : {&p->d_bundle_phase, &p->d_entry_phase, &p->d_plane_phase}) {
+  for (double **q :
+       {&p->d_bundle_phase, &p->d_entry_phase, &p->d_plane_phase, &p->d_tile_phase}) {
     if (*q) (void)hipFree(*q);
     *q = nullptr;
   }
   hipError_t e = upload(&p->d_bundle_phase, bph, &bytes);
   if (e == hipSuccess) e = upload(&p->d_plane_phase, pph, &bytes);
+  if (e == hipSuccess) e = upload(&p->d_tile_phase, tph, &bytes);
   if (e == hipSuccess) e = upload(&p->d_entry_phase, eph, &bytes);
   return e;
 }
@@ -364,6 +377,36 @@ sho::PlaneArgs make_plane_args(const sho_plan_s *p) {
   return A;
 }
 
+sho::TileArgs make_tile_args(const sho_plan_s *p) {
+  sho::TileArgs E;
+  E.atoms = p->d_atoms;
+  E.blocks = p->d_tblocks;
+  E.entries = p->d_tentries;
+  E.tab = p->d_tab;
+  E.u2_off = p->d_u2_off;
+  E.nu_atoms = p->d_nu_atoms;
+  E.phase = p->bloch ? p->d_tile_phase : nullptr;
+  E.nblocks = (int32_t)p->hp.tblocks.size();
+  E.natoms_u2 = (int32_t)p->hp.nu_atoms.size();
+  E.nx = p->hp.grid.n[0];
+  E.ny = p->hp.grid.n[1];
+  E.u2_scale = p->fp32 ? 2 : 1;
+  E.B = p->hp.nbands * E.u2_scale;
+  // two bands per lane halve the table reads per sum; one where that leaves
+  // fewer than two workgroups per CU (24^3, 3 atoms, cut-off 8, 24 bands, 96
+  // workgroups of two: 42.8 us, of one: 36.4)
+  E.nb = E.B > 16 && (int64_t)E.nblocks * ((E.B + 31) / 32) >= 512 ? 2 : 1;
+  // Non-temporal where a row of bands is whole cache lines (96^3, 160 atoms,
+  // 128 bands, cut-off 5: 463 us non-temporal, 501 not).  Where it is not, two
+  // band groups share lines, which the L2 puts together if they come one after
+  // the other (100 bands, cut-off 2: 510 us non-temporal with the groups apart,
+  // 338 this way; cut-off 5 547 and 428).
+  E.stream = (int64_t)E.B * (p->fp32 ? 4 : 8) % 128 == 0;
+  E.wide = (int64_t)E.B * (p->fp32 ? 4 : 8) % 16 == 0;
+  E.alpha = 1.0;
+  return E;
+}
+
 void prof_clear(sho_plan_s *p) {
   for (ProfEvent &ev : p->prof) {
     (void)hipEventDestroy(ev.a);
@@ -481,14 +524,16 @@ int64_t estimate_device_bytes(const sho::HostPlan &hp) {
   int64_t t = b(hp.natoms, sizeof(sho::AtomRec)) + b(nl, sizeof(sho::LineRec)) +
               b((int64_t)hp.bundles.size(), sizeof(sho::BundleRec)) +
               2 * b((int64_t)hp.work.size(), sizeof(sho::WorkRec)) +
-              b(hp.table_doubles, 8) + 2 * b(nl, 4) +
+              b(hp.table_doubles + 2 * sho::kTabPad, 8) + 2 * b(nl, 4) +
               b((int64_t)hp.rows.size(), sizeof(sho::RowRec)) + b(hp.natoms, 8) +
               b(hp.natoms, 4) + b(hp.u2_doubles, 8) +
               b((int64_t)hp.blocks.size(), sizeof(sho::BlockRec)) +
               b((int64_t)hp.entries.size(), sizeof(sho::EntryRec)) +
               b((int64_t)hp.run_desc.size(), 4) +
               b((int64_t)hp.punits.size(), sizeof(sho::PlaneUnit)) +
-              b((int64_t)hp.pbundles.size(), sizeof(sho::PlaneBundle));
+              b((int64_t)hp.pbundles.size(), sizeof(sho::PlaneBundle)) +
+              b((int64_t)hp.tblocks.size(), sizeof(sho::BlockRec)) +
+              b((int64_t)hp.tentries.size(), sizeof(sho::TileEntry));
   if (hp.flags & SHO_FLAG_STORED) {
     int64_t stored = 0;
     for (const auto &A : hp.atoms) stored += (int64_t)A.npoints * sho::stored_cols(hp, A);
@@ -500,15 +545,23 @@ int64_t estimate_device_bytes(const sho::HostPlan &hp) {
   return t;
 }
 
+// The tables of the default expansion: tiles where the plan can take them (the
+// shape that is reported is the one its mode has without them), else blocks.
 void build_default_blocks(sho::HostPlan *hp) {
-  if (hp->flags & SHO_FLAG_DETERMINISTIC) {
+  const bool det = (hp->flags & SHO_FLAG_DETERMINISTIC) != 0;
+  int32_t R = sho::owner_rows(*hp), X = 32;
+  if (det)
     hp->expand_mode = sho::kExpandOwner;
-    sho::build_blocks(hp, sho::owner_rows(*hp), 32);
+  else
+    sho::default_block_shape(*hp, &R, &X);
+  sho::build_tiles(hp);
+  if (hp->tile_form) {
+    hp->blk_rows = R;
+    hp->blk_x = X;
     return;
   }
-  int32_t R = 0, X = 0;
-  sho::default_block_shape(*hp, &R, &X);
   sho::build_blocks(hp, R, X);
+  if (det) return;
   // stored plans: the block form wins while the products are short (measured
   // up to nu_max = 2, 10 columns), the atom-owner form with atomics beyond
   const bool long_rows = hp->ncols > 0 ? hp->ncols > 10 : hp->nu_max > 2;
@@ -670,6 +723,18 @@ hipError_t run_expand(sho_plan_s *p, const void *c_v, void *psi_v, hipStream_t s
                       bool prof, double *u2_buf, double alpha = 1.0) {
   const double *c = static_cast<const double *>(c_v);
   double *psi = static_cast<double *>(psi_v);
+  if (p->hp.tile_form) {
+    sho::TileArgs E = make_tile_args(p);
+    E.alpha = alpha;
+    hipError_t e = timed(p, prof, SHO_KERNEL_EXPAND_Z, s, [&]() {
+      return sho::launch_tile_partials(p->hp.nu_max, p->fp32, E, c_v, u2_buf, s);
+    });
+    if (e == hipSuccess)
+      e = timed(p, prof, SHO_KERNEL_EXPAND_XY, s, [&]() {
+        return sho::launch_tiles(p->hp.nu_max, p->fp32, E, u2_buf, psi_v, s);
+      });
+    return e;
+  }
   if (p->fp32) {
     // FP32 plans: plane partials and the block form only
     sho::EArgs E = make_eargs(p);
@@ -807,10 +872,13 @@ sho_status finish_plan(sho_plan_s *p, uint32_t flags, int32_t nbands, bool f32,
   sho::build_rows(&p->hp);
   sho::build_planes(&p->hp);
   build_default_blocks(&p->hp);
-  std::vector<double> no_tab;
+  const int64_t tab_doubles = p->hp.table_doubles + 2 * sho::kTabPad;
+  double *d_tab = nullptr;
   if ((e = upload(&p->d_atoms, p->hp.atoms, &p->device_bytes)) != hipSuccess ||
       (e = upload(&p->d_lines, p->hp.lines, &p->device_bytes)) != hipSuccess ||
       (e = upload_schedule(p)) != hipSuccess || (e = upload_blocks(p)) != hipSuccess ||
+      (e = upload(&p->d_tblocks, p->hp.tblocks, &p->device_bytes)) != hipSuccess ||
+      (e = upload(&p->d_tentries, p->hp.tentries, &p->device_bytes)) != hipSuccess ||
       (e = upload(&p->d_punits, p->hp.punits, &p->device_bytes)) != hipSuccess ||
       (e = upload(&p->d_pbundles, p->hp.pbundles, &p->device_bytes)) != hipSuccess ||
       (e = upload(&p->d_doff, p->hp.dmat_off, &p->device_bytes)) != hipSuccess ||
@@ -819,16 +887,15 @@ sho_status finish_plan(sho_plan_s *p, uint32_t flags, int32_t nbands, bool f32,
       (e = upload(&p->d_rows, p->hp.rows, &p->device_bytes)) != hipSuccess ||
       (e = upload(&p->d_u2_off, p->hp.u2_off, &p->device_bytes)) != hipSuccess ||
       (e = upload(&p->d_nu_atoms, p->hp.nu_atoms, &p->device_bytes)) != hipSuccess ||
-      (e = hipMalloc((void **)&p->d_tab,
-                     std::max<int64_t>(p->hp.table_doubles, 1) * sizeof(double))) !=
-          hipSuccess) {
+      (e = hipMalloc((void **)&d_tab, tab_doubles * sizeof(double))) != hipSuccess) {
     free_plan_device(p);
     delete p;
     (void)hipGetLastError();
     return e == hipErrorOutOfMemory ? fail(SHO_E_NOMEM, "device allocation failed")
                                     : hip_fail(e, "plan upload");
   }
-  p->device_bytes += std::max<int64_t>(p->hp.table_doubles, 1) * sizeof(double);
+  p->d_tab = d_tab + sho::kTabPad;
+  p->device_bytes += tab_doubles * sizeof(double);
   e = sho::launch_tables(p->d_atoms, p->hp.natoms, p->hp.grid.h, p->d_tab, p->hp.m_max,
                          nullptr);
   if (e == hipSuccess && f32) {
@@ -1115,8 +1182,9 @@ sho_status sho_plan_get_info(sho_plan_t p, sho_plan_info *info) {
   info->device_bytes = (p->hp.flags & SHO_FLAG_HOST_ONLY)
                            ? estimate_device_bytes(p->hp)
                            : p->device_bytes + p->sched_bytes + p->blk_bytes;
-  info->expand_blocks = (int64_t)p->hp.blocks.size();
-  info->expand_entries = (int64_t)p->hp.entries.size();
+  info->expand_blocks = (int64_t)(p->hp.tile_form ? p->hp.tblocks : p->hp.blocks).size();
+  info->expand_entries =
+      (int64_t)(p->hp.tile_form ? p->hp.tentries.size() : p->hp.entries.size());
   info->stored_bytes = p->stored_bytes;
   info->union_points = p->hp.union_points;
   // the row kernel moves whole chunks of touched rows: with 32 or 64 bands
@@ -1414,6 +1482,19 @@ sho_status sho_plan_set_expand(sho_plan_t p, int32_t mode, int32_t block_rows,
     return fail(SHO_E_INVALID, "stored plans expand in the row or block form");
   if ((p->hp.flags & SHO_FLAG_DETERMINISTIC) && mode != sho::kExpandOwner)
     return fail(SHO_E_INVALID, "deterministic plans expand in the owner form only");
+  // a mode without a shape is the default again, which may run as tiles
+  const bool det = (p->hp.flags & SHO_FLAG_DETERMINISTIC) != 0;
+  if (block_rows == 0 && block_x == 0 && !p->hp.tblocks.empty() && p->hp.expand_tbe_shift < 0 &&
+      mode == (det ? sho::kExpandOwner : sho::kExpandBlocks)) {
+    int32_t R = sho::owner_rows(p->hp), X = 32;
+    if (!det) sho::default_block_shape(p->hp, &R, &X);
+    p->hp.blk_rows = R;
+    p->hp.blk_x = X;
+    p->hp.expand_mode = mode;
+    p->hp.tile_form = true;
+    p->sched_version++;
+    return SHO_OK;
+  }
   if (mode == sho::kExpandOwner) {
     const int32_t R = sho::owner_rows(p->hp);
     const int32_t X = block_x ? block_x : 32;
@@ -1446,6 +1527,7 @@ sho_status sho_plan_set_expand(sho_plan_t p, int32_t mode, int32_t block_rows,
     }
   }
   p->hp.expand_mode = mode;
+  p->hp.tile_form = false;
   p->sched_version++;
   return SHO_OK;
 }
@@ -1474,7 +1556,12 @@ sho_status sho_plan_set_expand_tile(sho_plan_t p, int32_t band_tile) {
     if (e != hipSuccess) return hip_fail(e, "hipDeviceSynchronize");
   }
   p->hp.expand_tbe_shift = tbs;
-  if (p->hp.expand_mode == sho::kExpandBlocks) {
+  p->hp.tile_form = false;
+  if (p->hp.expand_mode == sho::kExpandBlocks && tbs < 0 && !p->hp.tblocks.empty()) {
+    // the default tile again: the default form
+    sho::default_block_shape(p->hp, &p->hp.blk_rows, &p->hp.blk_x);
+    p->hp.tile_form = true;
+  } else if (p->hp.expand_mode == sho::kExpandBlocks) {
     int32_t R = 0, X = 0;
     sho::default_block_shape(p->hp, &R, &X);
     sho::build_blocks(&p->hp, R, X);
@@ -1504,6 +1591,7 @@ sho_status sho_plan_tune_expand(sho_plan_t p, const void *c, void *psi, int32_t 
   hipStream_t s = (hipStream_t)stream;
   struct Cand {
     int32_t mode, tbs, R, X;
+    bool tiles;
   };
   std::vector<Cand> cands;
   int nb_shift = 3;
@@ -1518,10 +1606,10 @@ sho_status sho_plan_tune_expand(sho_plan_t p, const void *c, void *psi, int32_t 
                            std::make_pair(R, std::max(1, X / 2)),
                            std::make_pair(std::min(256 / nfp, 2 * R), std::max(1, X / 2))})
       if (sho::block_shape_ok(p->hp, rx.first, rx.second))
-        cands.push_back({sho::kExpandBlocks, tbs, rx.first, rx.second});
+        cands.push_back({sho::kExpandBlocks, tbs, rx.first, rx.second, false});
     p->hp.expand_tbe_shift = keep;
   }
-  if (!p->fp32 && !p->bloch) cands.push_back({sho::kExpandRows, -1, 0, 0});
+  if (!p->fp32 && !p->bloch) cands.push_back({sho::kExpandRows, -1, 0, 0, false});
   hipEvent_t ea = nullptr, eb = nullptr;
   hipError_t e = hipEventCreate(&ea);
   if (e == hipSuccess) e = hipEventCreate(&eb);
@@ -1536,7 +1624,8 @@ sho_status sho_plan_tune_expand(sho_plan_t p, const void *c, void *psi, int32_t 
     *ms = (double)t / reps;
     return e1;
   };
-  const Cand before{p->hp.expand_mode, p->hp.expand_tbe_shift, p->hp.blk_rows, p->hp.blk_x};
+  const Cand before{p->hp.expand_mode, p->hp.expand_tbe_shift, p->hp.blk_rows, p->hp.blk_x,
+                    p->hp.tile_form};
   double ms_before = 0.0;
   if (e == hipSuccess) e = time_current(&ms_before);
   double best = ms_before;
@@ -1547,7 +1636,11 @@ sho_status sho_plan_tune_expand(sho_plan_t p, const void *c, void *psi, int32_t 
     if (e1 != hipSuccess) return e1;
     p->hp.expand_mode = cd.mode;
     p->hp.expand_tbe_shift = cd.tbs;
-    if (cd.mode == sho::kExpandBlocks) {
+    p->hp.tile_form = cd.tiles;
+    if (cd.tiles) {
+      p->hp.blk_rows = cd.R;
+      p->hp.blk_x = cd.X;
+    } else if (cd.mode == sho::kExpandBlocks) {
       sho::build_blocks(&p->hp, cd.R, cd.X);
       e1 = upload_blocks(p);
     }

@@ -12,6 +12,7 @@
 #pragma once
 
 #include <algorithm>
+#include <array>
 #include <cstdint>
 #include <string>
 #include <vector>
@@ -44,6 +45,7 @@ static_assert(sizeof(AtomRec) == 104, "AtomRec layout");
 // nf = nu + 2 (the derivative needs one function more than the basis).
 inline int32_t table_nf(int32_t nu) { return nu + 2; }
 inline int32_t table_nfp(int32_t nu) { return table_nf(nu) <= 8 ? 8 : 16; }
+constexpr int32_t table_nfp_c(int32_t nu) { return nu + 2 <= 8 ? 8 : 16; }
 
 // One z plane of one atom's support.
 struct PlaneRec {
@@ -166,6 +168,31 @@ struct EntryRec {
 };
 static_assert(sizeof(EntryRec) == 40, "EntryRec layout");
 
+// The tile form of the expansion: blocks of kTileRows rows x kTileX points of
+// one plane (four rows to a wave), an entry per atom plane and image touching
+// the block.
+constexpr int32_t kTileRows = 16;
+constexpr int32_t kTileX = 16;
+struct TileHead {
+  int64_t u2;          // first double of the atom plane's partials (band 0)
+  int32_t tab_x;       // table double of memory x = x0 (as in EntryRec)
+  int32_t tab_y;       // table double of block row 0
+  int16_t nu, nfp;
+  int8_t x_lo, x_hi;   // x rows of the table that exist, relative to x0
+  int8_t y_lo, y_hi;   // y rows that exist, relative to y0
+};
+// A wave's rows of an entry, 4 w + r for r = 0..3: 16 bits each, row 2 i in
+// the low half of d[i]: x begin | x end << 6 relative to x0 (0: no run); and
+// in bit t of steps whether points 2 t, 2 t + 1 are in any of the runs.
+struct TileWave {
+  uint32_t d[2];
+  uint32_t steps;
+};
+struct TileEntry : TileHead {
+  TileWave w[kTileRows / 4];
+};
+static_assert(sizeof(TileHead) == 24 && sizeof(TileEntry) == 72, "TileEntry layout");
+
 // Run descriptor of the block form: row r (relative to y0) | x begin << 8 |
 // x end << 16 (both relative to x0, end exclusive).
 inline uint32_t pack_run(int r, int xa, int xb) {
@@ -250,6 +277,11 @@ struct HostPlan {
   std::vector<uint32_t> run_desc;
   std::vector<int32_t> run_desc_run;    // the run of every descriptor
   std::vector<int64_t> desc_pbase;      // stored plans: P double of block x 0
+  bool tile_form = false;               // expand_mode's default runs as tiles
+  std::vector<BlockRec> tblocks;        // XCD-interleaved by plane
+  std::vector<TileEntry> tentries;
+  std::vector<std::array<int8_t, 3>> timages;  // Bloch plans: periodic image of
+                                               // every entry (as in EntryRec)
   int32_t proj_form = 0;                // kProjectItems or kProjectBlocks
   bool plane_form = false;              // item form's plan runs the plane form
   int32_t plane_lds_rows = 0;           // x table rows of a unit, largest
@@ -353,6 +385,10 @@ void build_work(HostPlan *P, int tb_shift, int64_t target_points, int32_t sched)
 // the plane partials U2[jz][pair][band].
 void build_rows(HostPlan *P);
 
+// The 1D tables lie in memory with a block's worth of doubles before and after
+// them: the tile kernel copies whole blocks of rows of an atom's table.
+constexpr int64_t kTabPad = 32 * 16;
+
 // Limits of the plane form: bytes of a memory plane of psi and of an atom's
 // widest line (32-bit offsets, bit 31 marks lanes without a value), x table rows of an atom in LDS (at most
 // 12 functions of 8 bytes each per row) and bundles of a unit (72 bytes each).
@@ -397,6 +433,11 @@ inline int plane_waves(const HostPlan &P) {
 // should run.
 // Needs the offsets of the plane partials (build_rows) too.
 void build_planes(HostPlan *P);
+
+// Blocks and entries of the tile form of the expansion (needs build_rows);
+// sets tile_form and block_points.  Nothing is built for plans that cannot
+// take the form.
+void build_tiles(HostPlan *P);
 
 // Blocks of R rows x X points for the block form of the expansion (needs
 // build_rows for run_atom).

@@ -94,6 +94,28 @@ struct PlaneArgs {
   double h3;
 };
 
+// Argument block of the tile form of the expansion.
+struct TileArgs {
+  const AtomRec *atoms;
+  const BlockRec *blocks;
+  const TileEntry *entries;
+  const double *tab;          // 1D tables of all atoms (FP64 for either type)
+  const int64_t *u2_off;      // [natoms] first partial of the atom, in units of
+                              // u2_scale values
+  const int32_t *nu_atoms;    // atoms with a support
+  const double *phase;        // Bloch plans: (cos, sin) of k.T per entry
+  int32_t nblocks;            // a multiple of kXcds
+  int32_t natoms_u2;
+  int32_t nx, ny;
+  int32_t B;                  // real values per grid point
+  int32_t groups;             // band groups of a tile (set by the launch)
+  int32_t nb;                 // adjacent bands per lane (1 or 2)
+  int32_t u2_scale;           // 2 for FP32 plans (offsets count band pairs)
+  int32_t stream;             // 1: psi past the caches (non-temporal)
+  int32_t wide;               // 1: rows of partials are whole 16-byte pieces
+  double alpha;               // psi += alpha * sum_n c P_n
+};
+
 // Argument block of the stored-projector kernels.
 struct SArgs {
   const AtomRec *atoms;
@@ -198,6 +220,14 @@ hipError_t static_scratch(double **ptr);
 // float if f32, else double.
 hipError_t launch_project_planes(int nu_max, bool f32, const PlaneArgs &P, const void *psi,
                                  void *p2, void *c, hipStream_t s);
+
+// Tile form of the expansion: plane partials of c into u2 (pairs in nx-major
+// order, so not those of launch_expand_planes), then the blocks.  c, u2 and
+// psi are float if f32, else double.
+hipError_t launch_tile_partials(int nu_max, bool f32, const TileArgs &E, const void *c, void *u2,
+                                hipStream_t s);
+hipError_t launch_tiles(int nu_max, bool f32, const TileArgs &E, const void *u2, void *psi,
+                        hipStream_t s);
 
 // FP32 plans (an even number of bands, processed as pairs: K.B and E.B count
 // pairs).  tab: the plan's tables rounded to FP32.

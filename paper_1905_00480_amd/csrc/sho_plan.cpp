@@ -870,6 +870,142 @@ void build_block_set(const HostPlan *P, int32_t R, int32_t X, BlockSet *out) {
       out->points += (int64_t)(std::min(B.y0 + R, ny) - B.y0) * (std::min(B.x0 + X, nx) - B.x0);
 }
 
+void build_tiles(HostPlan *P) {
+  P->tile_form = false;
+  P->tblocks.clear();
+  P->tentries.clear();
+  P->timages.clear();
+  if (P->flags & (SHO_FLAG_STORED | SHO_FLAG_PER_ATOM)) return;
+  const int32_t nx = P->grid.n[0], ny = P->grid.n[1], nz = P->grid.n[2];
+  // a memory plane is addressed by 32-bit byte offsets, the tables by 32-bit
+  // indices
+  if ((int64_t)nx * ny * P->nbands * 8 > kPlaneMaxBytes ||
+      P->table_doubles > std::numeric_limits<int32_t>::max())
+    return;
+  const int32_t nyb = (ny + kTileRows - 1) / kTileRows, nxb = (nx + kTileX - 1) / kTileX;
+  constexpr int32_t kNu = SHO_NU_MAX + 1;
+  if ((int64_t)nz * nyb * nxb * kNu >= std::numeric_limits<int32_t>::max() / 2) return;
+  // Where the block form is kept (deterministic plans never: their other form,
+  // whole rows owned by a workgroup, is slower throughout).
+  if (!(P->flags & SHO_FLAG_DETERMINISTIC)) {
+    const bool f32 = (P->flags & SHO_FLAG_FP32) != 0;
+    const int64_t values = (int64_t)P->nbands * (f32 ? 2 : 1);  // per grid point
+    // A few small workgroups: one launch against two. 48^3, 20 atoms, cut-off
+    // 2, 12 bands (432 tiles): tiles / blocks 21.7 / 19.4 us, 32 bands 23.7 / 26.6
+    if (P->nu_max <= 3 && (int64_t)nz * nyb * nxb * ((values + 15) / 16) < 512) return;
+    // Up to 8 values leave half of a tile's 16 band lanes idle, while a block's
+    // go to more points: 128^3, 380 atoms, 4 bands, tiles / blocks 70 / 63 us
+    // (cut-off 2), 127 / 116 (5), but 230 / 329 (8).  FP32 blocks convert and
+    // compute in FP64 as well: 71 / 108 (2), 130 / 177 (5).
+    if (!f32 && values <= 8 && P->nu_max <= 5) return;
+    // Cut-offs 0 and 1 are bound by psi, and band groups share the cache lines
+    // of rows that are not whole lines: 128^3, 380 atoms, 36 bands, tiles /
+    // blocks 286 / 217 us (cut-off 0), 316 / 298 (1), 335 / 365 (2); FP32, 96^3,
+    // 160 atoms, 100 bands 232 / 253 (1).
+    if (!f32 && values > 16 && values % 16 != 0 && P->nu_max <= 1) return;
+  }
+  std::vector<TileEntry> ents;
+  std::vector<std::array<int8_t, 3>> images;
+  std::vector<int32_t> key;  // block * kNu + nu
+  for (int32_t a = 0; a < P->natoms; ++a) {
+    const AtomRec &A = P->atoms[a];
+    const int64_t np = (int64_t)(A.nu + 1) * (A.nu + 2) / 2;
+    for (int32_t pi = A.plane_begin; pi < A.plane_begin + A.nplanes; ++pi) {
+      const int32_t rb = P->planes[pi].line_begin;
+      const int32_t re = (pi + 1 < A.plane_begin + A.nplanes) ? P->planes[pi + 1].line_begin
+                                                              : A.line_begin + A.nlines;
+      const size_t first = ents.size();
+      for (int32_t r = rb; r < re; ++r) {
+        const LineRec &L = P->lines[r];
+        const int32_t z = L.row / ny, y = L.row % ny, row = y % kTileRows;
+        for (int32_t cx = L.x0m / kTileX; cx <= (L.x0m + L.len - 1) / kTileX; ++cx) {
+          const int32_t k = ((z * nyb + y / kTileRows) * nxb + cx) * kNu + A.nu;
+          const int32_t x0 = cx * kTileX, y0 = y - row;
+          const int32_t jx0 = x0 + L.jx0 - L.x0m, jy0 = y0 + L.jy - y;
+          const int32_t tab_x = (int32_t)(A.tab_off + (int64_t)jx0 * A.tab_nfp);
+          const int32_t tab_y = (int32_t)(A.tab_off + (int64_t)(A.mx + jy0) * A.tab_nfp);
+          const uint32_t range = (uint32_t)(std::max(L.x0m, x0) - x0) |
+                                 (uint32_t)(std::min(L.x0m + L.len, x0 + kTileX) - x0) << 6;
+          const int wave = row / 4, r4 = row % 4, sh = 16 * (r4 & 1);
+          const bool bloch = (P->flags & SHO_FLAG_BLOCH) != 0;
+          size_t i = ents.size();
+          while (i > first) {  // runs of one block and image share an entry
+            const TileEntry &E = ents[i - 1];
+            if (key[i - 1] == k && E.tab_x == tab_x && E.tab_y == tab_y &&
+                !((E.w[wave].d[r4 / 2] >> sh) & 0xffff))
+              break;
+            --i;
+          }
+          if (i == first) {
+            TileEntry E{};
+            E.u2 = P->u2_off[a] + (int64_t)L.jz * np * P->nbands;
+            E.tab_x = tab_x;
+            E.tab_y = tab_y;
+            E.nu = (int16_t)A.nu;
+            E.nfp = (int16_t)A.tab_nfp;
+            E.x_lo = (int8_t)std::max(0, -jx0);
+            E.x_hi = (int8_t)std::min(kTileX, A.mx - jx0);
+            E.y_lo = (int8_t)std::max(0, -jy0);
+            E.y_hi = (int8_t)std::min(kTileRows, A.my - jy0);
+            if (bloch) {
+              const int64_t img[3] = {((int64_t)A.ix0 + L.jx0 - L.x0m) / nx,
+                                      ((int64_t)A.iy0 + L.jy - y) / ny,
+                                      ((int64_t)A.iz0 + L.jz - z) / nz};
+              std::array<int8_t, 3> m;
+              for (int d = 0; d < 3; ++d)
+                m[d] = (int8_t)std::min<int64_t>(std::max<int64_t>(img[d], -127), 127);
+              images.push_back(m);
+            }
+            ents.push_back(E);
+            key.push_back(k);
+            i = ents.size();
+          }
+          ents[i - 1].w[wave].d[r4 / 2] |= range << sh;
+        }
+      }
+    }
+  }
+  if (ents.size() > (size_t)std::numeric_limits<int32_t>::max()) return;
+  // by block, then cut-off (the kernel's loops), then plan order
+  std::vector<int32_t> begin((size_t)nz * nyb * nxb * kNu + 1, 0);
+  for (int32_t k : key) ++begin[k + 1];
+  for (size_t k = 1; k < begin.size(); ++k) begin[k] += begin[k - 1];
+  std::vector<int32_t> at(begin.begin(), begin.end() - 1);
+  for (TileEntry &E : ents)
+    for (TileWave &w : E.w)
+      for (int r = 0; r < 4; ++r) {
+        const uint32_t d = (w.d[r / 2] >> (16 * (r & 1))) & 0xffff;
+        const int xa = d & 0x3f, xb = d >> 6;
+        for (int t = 0; t < kTileX / 2; ++t)
+          if (xa < 2 * t + 2 && xb > 2 * t) w.steps |= 1u << t;
+      }
+  P->tentries.resize(ents.size());
+  P->timages.resize(images.size());
+  for (size_t i = 0; i < ents.size(); ++i) {
+    const int32_t to = at[key[i]]++;
+    P->tentries[to] = ents[i];
+    if (!images.empty()) P->timages[to] = images[i];
+  }
+  // blocks of planes z = k mod 8 go to workgroups g = k mod 8 (XCD k)
+  std::vector<BlockRec> cls[kXcds];
+  P->block_points = 0;
+  for (int32_t b = 0; b < nz * nyb * nxb; ++b) {
+    const int32_t e0 = begin[(size_t)b * kNu], n = begin[(size_t)(b + 1) * kNu] - e0;
+    if (!n) continue;
+    const int32_t z = b / (nyb * nxb);
+    const BlockRec B{z, b / nxb % nyb * kTileRows, b % nxb * kTileX, e0, n, 0};
+    cls[z % kXcds].push_back(B);
+    P->block_points += (int64_t)(std::min(B.y0 + kTileRows, ny) - B.y0) *
+                       (std::min(B.x0 + kTileX, nx) - B.x0);
+  }
+  size_t most = 0;
+  for (const auto &c : cls) most = std::max(most, c.size());
+  const BlockRec pad{0, 0, 0, 0, -1, 0};
+  for (size_t i = 0; i < most; ++i)
+    for (const auto &c : cls) P->tblocks.push_back(i < c.size() ? c[i] : pad);
+  P->tile_form = true;
+}
+
 void build_blocks(HostPlan *P, int32_t R, int32_t X) {
   BlockSet bs;
   build_block_set(P, R, X, &bs);
