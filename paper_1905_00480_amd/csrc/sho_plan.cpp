@@ -606,11 +606,19 @@ void build_planes(HostPlan *P) {
   // x 115, 272 atoms of cut-off 3, 2 bands: whole step 65 us against 68).
   // Single precision with little overlap: half the bytes to save, the same z
   // pass to pay (128^3, 512 atoms, 32 bands: items 0.118 ms, planes 0.150).
+  // Up to 8 bands leave half of a wave's lanes idle, and with enough atoms the
+  // item form fills the chip as well: items / planes at 128^3, 380 atoms, 34 / 60
+  // us (cut-off 3, 2 bands), 55 / 60 (3, 8), 77 / 105 (5, 4), 100 / 98 (5, 8), 222
+  // / 210 (8, 2); at 96^3, 160 atoms, 29 / 35 (3, 4), 41 / 35 (3, 8), 64 / 56 (5, 4).
   int64_t largest = 0;
   for (const AtomRec &A : P->atoms) largest = std::max(largest, A.npoints);
   const bool f32 = (P->flags & SHO_FLAG_FP32) != 0;
   const int32_t bands = P->nbands * (f32 ? 2 : 1);
-  P->plane_form = !((all.size() <= 64 || bands <= 8) && largest <= 4096) &&
+  const int64_t units = (int64_t)all.size();
+  const bool many = bands <= 8 && (P->nu_max <= 3 ? units >= 640 * bands
+                                                  : P->nu_max <= 5 && bands <= 4 &&
+                                                        units >= 8192);
+  P->plane_form = !((units <= 64 || bands <= 8) && largest <= 4096) && !many &&
                   !(f32 && P->support_points < 4 * P->union_points);
 }
 
