@@ -1833,7 +1833,8 @@ sho_status check_multiply(const sho_plan_s *p, const double *D, const double *c,
 
 hipError_t run_multiply(sho_plan_s *p, const double *D, const double *c, double *d,
                         hipStream_t s) {
-  return sho::launch_multiply(p->d_atoms, p->hp.natoms, p->d_doff, D, c, d, p->hp.nbands, s);
+  return sho::launch_multiply(p->d_atoms, p->hp.natoms, p->hp.nu_max, p->d_doff, D, c, d,
+                              p->hp.nbands, s);
 }
 
 }  // namespace

@@ -1613,14 +1613,15 @@ __global__ __launch_bounds__(kBlkBlock) void k_expand_blocks_stored(
 
 // d[a][n][b] = sum_m D_a[n][m] c[a][m][b] (sec. 3.2 step 2 with the atomic
 // matrix carried into the SHO basis, sec. 3.5): per atom a dense N x N times
-// N x B product, on FP64 MFMA with i = n, j = b and four m per step.  One
-// workgroup per (atom, 32-band tile); wave w takes the 16-row blocks
-// w, w+4, ...
-__global__ __launch_bounds__(kStoredBlock) void k_multiply(const AtomRec *__restrict__ atoms,
-                                                           const int64_t *__restrict__ doff,
-                                                           const double *__restrict__ D,
-                                                           const double *__restrict__ c,
-                                                           double *__restrict__ d, int32_t B) {
+// N x B product, on FP64 MFMA with i = n, j = b and four m per step.
+//
+// Many atoms: one workgroup per (atom, 32-band tile); wave w takes the 16-row
+// blocks w, w+4, ...
+__global__ __launch_bounds__(kStoredBlock) void k_multiply_rows(const AtomRec *__restrict__ atoms,
+                                                                const int64_t *__restrict__ doff,
+                                                                const double *__restrict__ D,
+                                                                const double *__restrict__ c,
+                                                                double *__restrict__ d, int32_t B) {
   const int a = blockIdx.x;
   const int nu = load_uniform(&atoms[a].nu);
   const int64_t row0 = load_uniform(&atoms[a].coeff_row);
@@ -1654,6 +1655,72 @@ __global__ __launch_bounds__(kStoredBlock) void k_multiply(const AtomRec *__rest
       }
     }
   }
+}
+
+// Few atoms: one workgroup per (atom, 32-band tile, 16 rows); the waves take a
+// quarter of the m each, in batches whose loads are in flight together, and
+// their sums are added in wave order.  Bound by the latency of D and c: 8 atoms
+// of cut-offs 0..9 and 21 bands took 64.4 us by row blocks and take 4.6 this way.
+__global__ __launch_bounds__(kStoredBlock) void k_multiply(const AtomRec *__restrict__ atoms,
+                                                           const int64_t *__restrict__ doff,
+                                                           const double *__restrict__ D,
+                                                           const double *__restrict__ c,
+                                                           double *__restrict__ d, int32_t B) {
+  constexpr int kWavesM = kStoredBlock / 64, kBatch = 4;
+  static_assert(kWavesM == 4, "one accumulator register per wave in the last sum");
+  __shared__ double part[kWavesM][8][64];
+  const int a = blockIdx.x;
+  const int nu = load_uniform(&atoms[a].nu);
+  const int N = (nu + 1) * (nu + 2) * (nu + 3) / 6;
+  const int n0 = blockIdx.z * 16;
+  if (n0 >= N) return;
+  const int64_t row0 = load_uniform(&atoms[a].coeff_row);
+  const double *Da = D + doff[a];
+  const int lane = threadIdx.x & 63;
+  const int w = wave_id();
+  const int q = lane >> 4, col = lane & 15;
+  const int b0 = blockIdx.y * kStoredTile;
+  const int bA = b0 + col, bB = b0 + 16 + col;
+  const bool okA = bA < B, okB = bB < B, okN = n0 + col < N;
+  const double *Dn = Da + (int64_t)min(n0 + col, N - 1) * N;
+  const double *cA = c + row0 * B + min(bA, B - 1), *cB = c + row0 * B + min(bB, B - 1);
+  const int steps = ((N + 3) / 4 + kWavesM - 1) / kWavesM;  // of a wave
+  const int end = min(N, 4 * steps * (w + 1));
+  dx4 acc0 = {0.0, 0.0, 0.0, 0.0}, acc1 = {0.0, 0.0, 0.0, 0.0};
+  for (int m0 = 4 * steps * w; m0 < end; m0 += 4 * kBatch) {
+    double av[kBatch], va[kBatch], vb[kBatch];
+#pragma unroll
+    for (int k = 0; k < kBatch; ++k) {
+      const int m = min(m0 + 4 * k + q, N - 1);
+      av[k] = Dn[m];
+      va[k] = cA[(int64_t)m * B];
+      vb[k] = cB[(int64_t)m * B];
+    }
+#pragma unroll
+    for (int k = 0; k < kBatch; ++k) {
+      const bool in = m0 + 4 * k + q < end;
+      const double x = in && okN ? av[k] : 0.0;
+      acc0 = mfma_f64(x, in && okA ? va[k] : 0.0, acc0);
+      acc1 = mfma_f64(x, in && okB ? vb[k] : 0.0, acc1);
+    }
+  }
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    part[w][r][lane] = acc0[r];
+    part[w][4 + r][lane] = acc1[r];
+  }
+  __syncthreads();
+  // register w of every wave: row 4 w + q
+  const int n = n0 + 4 * w + q;
+  if (n >= N) return;
+  double sA = 0.0, sB = 0.0;
+#pragma unroll
+  for (int k = 0; k < kWavesM; ++k) {
+    sA += part[k][w][lane];
+    sB += part[k][4 + w][lane];
+  }
+  if (okA) d[(row0 + n) * B + bA] = sA;
+  if (okB) d[(row0 + n) * B + bB] = sB;
 }
 
 // ------------------------------------------------------------- derivative --
@@ -2073,12 +2140,23 @@ hipError_t launch_expand_stored(const SArgs &S, const double *c, double *psi,
   return hipErrorInvalidValue;
 }
 
-hipError_t launch_multiply(const AtomRec *atoms, int32_t natoms, const int64_t *doff,
-                           const double *D, const double *c, double *d, int32_t B,
-                           hipStream_t s) {
+hipError_t launch_multiply(const AtomRec *atoms, int32_t natoms, int32_t nu_max,
+                           const int64_t *doff, const double *D, const double *c, double *d,
+                           int32_t B, hipStream_t s) {
   if (natoms <= 0) return hipSuccess;
-  const dim3 g((unsigned)natoms, (unsigned)((B + kStoredTile - 1) / kStoredTile));
-  hipLaunchKernelGGL(k_multiply, g, dim3(kStoredBlock), 0, s, atoms, doff, D, c, d, B);
+  const int32_t rows = (nu_max + 1) * (nu_max + 2) * (nu_max + 3) / 6;
+  const unsigned tiles = (unsigned)((B + kStoredTile - 1) / kStoredTile);
+  const int64_t wgs = (int64_t)natoms * tiles;
+  // Row blocks where (atom, tile) pairs alone fill the chip and the waves' parts
+  // of m are short.  Row blocks / split, us: 100 atoms of cut-off 6, 32 bands 13.9
+  // / 10.9, 400 atoms 24.8 / 13.5, 1500 atoms 39.0 / 47.9; 1500 atoms of cut-offs
+  // 0..9, 32 bands 140 / 69, 9, 32 bands 301 / 303, 9, 100 bands 1215 / 1289.
+  if (wgs > (nu_max >= 8 ? 4096 : 1024))
+    hipLaunchKernelGGL(k_multiply_rows, dim3((unsigned)natoms, tiles), dim3(kStoredBlock), 0, s,
+                       atoms, doff, D, c, d, B);
+  else
+    hipLaunchKernelGGL(k_multiply, dim3((unsigned)natoms, tiles, (unsigned)((rows + 15) / 16)),
+                       dim3(kStoredBlock), 0, s, atoms, doff, D, c, d, B);
   return hipGetLastError();
 }
 

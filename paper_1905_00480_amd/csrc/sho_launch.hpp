@@ -195,9 +195,9 @@ hipError_t launch_project_stored(const SArgs &S, const double *psi, double *c,
 hipError_t launch_expand_stored(const SArgs &S, const double *c, double *psi,
                                 hipStream_t s);
 // d = D c per atom (D: per-atom N x N row-major blocks at doff[a]).
-hipError_t launch_multiply(const AtomRec *atoms, int32_t natoms, const int64_t *doff,
-                           const double *D, const double *c, double *d, int32_t B,
-                           hipStream_t s);
+hipError_t launch_multiply(const AtomRec *atoms, int32_t natoms, int32_t nu_max,
+                           const int64_t *doff, const double *D, const double *c, double *d,
+                           int32_t B, hipStream_t s);
 // grad must be zeroed first (launch_fill).  With K.det, every (atom, band
 // tile) writes its three sums to gpart[(atom * ntiles + tile) * 3 + d]
 // instead, and launch_force_sum adds them in tile order into grad.

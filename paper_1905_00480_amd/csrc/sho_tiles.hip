@@ -97,8 +97,9 @@ __device__ inline void store_bands(__amdgpu_buffer_rsrc_t r, uint32_t off, const
 // U2[jz][p][b] = alpha sum_nz phi_nz(z_jz) C[nx,ny,nz][b] for every plane jz of
 // every atom, pairs p with nx outer and ny inner (the order in which the tile
 // kernel's lanes read four ny of one nx), for all cut-offs in one launch.
-// One workgroup per (atom, 16 NB bands): the coefficients in LDS, a thread
-// writes all pairs of one plane and NB bands.  Bound by the write.
+// One workgroup per (atom, 16 NB bands, part of the planes): the coefficients
+// in LDS, a thread writes all pairs of one plane and NB bands.  Bound by the
+// write.
 template <typename T, int NB>
 struct __attribute__((aligned(NB * sizeof(T)))) Bands {
   T v[NB];
@@ -127,7 +128,7 @@ __device__ inline void partials_atom(const TileArgs &E, int a, const AtomRec &A,
   __syncthreads();
   const double *tz = E.tab + A.tab_off + (int64_t)(A.mx + A.my) * A.tab_nfp;
   T *dst = u2 + E.u2_off[a] * E.u2_scale;
-  for (int t = threadIdx.x; t < A.mz * 16; t += kThreads) {
+  for (int t = threadIdx.x + blockIdx.z * kThreads; t < A.mz * 16; t += gridDim.z * kThreads) {
     const int bl = t & 15, jz = t >> 4;
     const int b = b0 + bl * NB;
     if (b >= E.B) continue;
@@ -554,7 +555,12 @@ static hipError_t launch_tiles_nb(const TileArgs &E, const void *u2, void *psi, 
 template <typename T, int NUMAX, int NB>
 static hipError_t launch_partials_nb(const TileArgs &E, const void *c, void *u2, hipStream_t s) {
   constexpr int NS = (NUMAX + 1) * (NUMAX + 2) * (NUMAX + 3) / 6;
-  const dim3 g((unsigned)E.natoms_u2, (unsigned)((E.B + 16 * NB - 1) / (16 * NB)));
+  // An atom's planes in up to four parts where (atom, band group) pairs do not
+  // fill the chip: 8 atoms of cut-offs 0..9, 21 bands 16.2 us in one part, 7.7 in
+  // four; 6 atoms of cut-off 5, 32 bands 5.4 and 4.5.
+  const unsigned groups = (unsigned)((E.B + 16 * NB - 1) / (16 * NB));
+  const int64_t wgs = (int64_t)E.natoms_u2 * groups;
+  const dim3 g((unsigned)E.natoms_u2, groups, wgs >= 256 ? 1 : wgs >= 128 ? 2 : 4);
   hipLaunchKernelGGL((k_partials<T, NUMAX, NB>), g, dim3(kThreads), NS * 16 * NB * sizeof(T), s,
                      E, static_cast<const T *>(c), static_cast<T *>(u2));
   return hipGetLastError();
