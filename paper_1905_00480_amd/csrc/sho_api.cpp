@@ -95,6 +95,7 @@ struct sho_plan_s {
   int64_t pblk_bytes = 0;
   sho::BlockRec *d_tblocks = nullptr;    // tile form of the expansion
   sho::TileEntry *d_tentries = nullptr;
+  uint16_t *d_tcover = nullptr;
   double *d_tile_phase = nullptr;        // Bloch plans: (cos, sin) per entry
   sho::PlaneUnit *d_punits = nullptr;    // plane form of the projection
   sho::PlaneBundle *d_pbundles = nullptr;
@@ -135,8 +136,10 @@ void free_plan_device(sho_plan_s *p) {
   }
   if (p->d_tblocks) (void)hipFree(p->d_tblocks);
   if (p->d_tentries) (void)hipFree(p->d_tentries);
+  if (p->d_tcover) (void)hipFree(p->d_tcover);
   p->d_tblocks = nullptr;
   p->d_tentries = nullptr;
+  p->d_tcover = nullptr;
   if (p->d_punits) (void)hipFree(p->d_punits);
   if (p->d_pbundles) (void)hipFree(p->d_pbundles);
   p->d_punits = nullptr;
@@ -382,6 +385,7 @@ sho::TileArgs make_tile_args(const sho_plan_s *p) {
   E.atoms = p->d_atoms;
   E.blocks = p->d_tblocks;
   E.entries = p->d_tentries;
+  E.cover = p->d_tcover;
   E.tab = p->d_tab;
   E.u2_off = p->d_u2_off;
   E.nu_atoms = p->d_nu_atoms;
@@ -400,7 +404,7 @@ sho::TileArgs make_tile_args(const sho_plan_s *p) {
   // 128 bands, cut-off 5: 463 us non-temporal, 501 not).  Where it is not, two
   // band groups share lines, which the L2 puts together if they come one after
   // the other (100 bands, cut-off 2: 510 us non-temporal with the groups apart,
-  // 338 this way; cut-off 5 547 and 428).
+  // 338 this way; both with whole tiles moved).
   E.stream = (int64_t)E.B * (p->fp32 ? 4 : 8) % 128 == 0;
   E.wide = (int64_t)E.B * (p->fp32 ? 4 : 8) % 16 == 0;
   E.alpha = 1.0;
@@ -533,7 +537,8 @@ int64_t estimate_device_bytes(const sho::HostPlan &hp) {
               b((int64_t)hp.punits.size(), sizeof(sho::PlaneUnit)) +
               b((int64_t)hp.pbundles.size(), sizeof(sho::PlaneBundle)) +
               b((int64_t)hp.tblocks.size(), sizeof(sho::BlockRec)) +
-              b((int64_t)hp.tentries.size(), sizeof(sho::TileEntry));
+              b((int64_t)hp.tentries.size(), sizeof(sho::TileEntry)) +
+              b((int64_t)hp.tcover.size(), sizeof(uint16_t));
   if (hp.flags & SHO_FLAG_STORED) {
     int64_t stored = 0;
     for (const auto &A : hp.atoms) stored += (int64_t)A.npoints * sho::stored_cols(hp, A);
@@ -879,6 +884,7 @@ sho_status finish_plan(sho_plan_s *p, uint32_t flags, int32_t nbands, bool f32,
       (e = upload_schedule(p)) != hipSuccess || (e = upload_blocks(p)) != hipSuccess ||
       (e = upload(&p->d_tblocks, p->hp.tblocks, &p->device_bytes)) != hipSuccess ||
       (e = upload(&p->d_tentries, p->hp.tentries, &p->device_bytes)) != hipSuccess ||
+      (e = upload(&p->d_tcover, p->hp.tcover, &p->device_bytes)) != hipSuccess ||
       (e = upload(&p->d_punits, p->hp.punits, &p->device_bytes)) != hipSuccess ||
       (e = upload(&p->d_pbundles, p->hp.pbundles, &p->device_bytes)) != hipSuccess ||
       (e = upload(&p->d_doff, p->hp.dmat_off, &p->device_bytes)) != hipSuccess ||

@@ -282,6 +282,7 @@ struct HostPlan {
   std::vector<TileEntry> tentries;
   std::vector<std::array<int8_t, 3>> timages;  // Bloch plans: periodic image of
                                                // every entry (as in EntryRec)
+  std::vector<uint16_t> tcover;         // [tile][row]: bit x where a support is
   int32_t proj_form = 0;                // kProjectItems or kProjectBlocks
   bool plane_form = false;              // item form's plan runs the plane form
   int32_t plane_lds_rows = 0;           // x table rows of a unit, largest

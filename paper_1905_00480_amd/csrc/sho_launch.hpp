@@ -99,6 +99,7 @@ struct TileArgs {
   const AtomRec *atoms;
   const BlockRec *blocks;
   const TileEntry *entries;
+  const uint16_t *cover;      // [block][row]: bit x where a support holds the point
   const double *tab;          // 1D tables of all atoms (FP64 for either type)
   const int64_t *u2_off;      // [natoms] first partial of the atom, in units of
                               // u2_scale values

@@ -883,6 +883,7 @@ void build_tiles(HostPlan *P) {
   P->tblocks.clear();
   P->tentries.clear();
   P->timages.clear();
+  P->tcover.clear();
   if (P->flags & (SHO_FLAG_STORED | SHO_FLAG_PER_ATOM)) return;
   const int32_t nx = P->grid.n[0], ny = P->grid.n[1], nz = P->grid.n[2];
   // a memory plane is addressed by 32-bit byte offsets, the tables by 32-bit
@@ -898,23 +899,22 @@ void build_tiles(HostPlan *P) {
   if (!(P->flags & SHO_FLAG_DETERMINISTIC)) {
     const bool f32 = (P->flags & SHO_FLAG_FP32) != 0;
     const int64_t values = (int64_t)P->nbands * (f32 ? 2 : 1);  // per grid point
-    // A few small workgroups: one launch against two. 48^3, 20 atoms, cut-off
-    // 2, 12 bands (432 tiles): tiles / blocks 21.7 / 19.4 us, 32 bands 23.7 / 26.6
-    if (P->nu_max <= 3 && (int64_t)nz * nyb * nxb * ((values + 15) / 16) < 512) return;
-    // Up to 8 values leave half of a tile's 16 band lanes idle, while a block's
-    // go to more points: 128^3, 380 atoms, 4 bands, tiles / blocks 70 / 63 us
-    // (cut-off 2), 127 / 116 (5), but 230 / 329 (8).  FP32 blocks convert and
-    // compute in FP64 as well: 71 / 108 (2), 130 / 177 (5).
-    if (!f32 && values <= 8 && P->nu_max <= 5) return;
-    // Cut-offs 0 and 1 are bound by psi, and band groups share the cache lines
-    // of rows that are not whole lines: 128^3, 380 atoms, 36 bands, tiles /
-    // blocks 286 / 217 us (cut-off 0), 316 / 298 (1), 335 / 365 (2); FP32, 96^3,
-    // 160 atoms, 100 bands 232 / 253 (1).
-    if (!f32 && values > 16 && values % 16 != 0 && P->nu_max <= 1) return;
+    // One band group of few tiles and small cut-offs: a tile's chain of entries
+    // is not hidden.  64^3, 48 atoms, cut-off 2, 8 bands (1024 tiles) tiles /
+    // blocks 23.7 / 21.3 us; 96^3, 160 atoms (3456) 38.1 / 38.4; 24^3, 3 atoms, 32
+    // bands 15.9 / 16.8.
+    if (values <= 16 && P->nu_max <= 3 && (int64_t)nz * nyb * nxb < 2048) return;
+    // Up to 4 values leave most of a tile's 16 band lanes idle, while a block's
+    // go to more points: 128^3, 380 atoms, 4 bands, tiles / blocks 68 / 63 us
+    // (cut-off 2), 115 / 114 (5), but 230 / 329 (8); 8 bands 69 / 71 (2), 120 / 123
+    // (5).  FP32 blocks compute in FP64 as well: 70 / 108 (2, 4 bands).
+    if (!f32 && values <= 4 && P->nu_max <= 5) return;
   }
   std::vector<TileEntry> ents;
   std::vector<std::array<int8_t, 3>> images;
   std::vector<int32_t> key;  // block * kNu + nu
+  // bit x of [block][row]: a support holds the point
+  std::vector<uint16_t> cover((size_t)nz * nyb * nxb * kTileRows, 0);
   for (int32_t a = 0; a < P->natoms; ++a) {
     const AtomRec &A = P->atoms[a];
     const int64_t np = (int64_t)(A.nu + 1) * (A.nu + 2) / 2;
@@ -936,6 +936,8 @@ void build_tiles(HostPlan *P) {
                                  (uint32_t)(std::min(L.x0m + L.len, x0 + kTileX) - x0) << 6;
           const int wave = row / 4, r4 = row % 4, sh = 16 * (r4 & 1);
           const bool bloch = (P->flags & SHO_FLAG_BLOCH) != 0;
+          cover[(size_t)(k / kNu) * kTileRows + row] |=
+              (uint16_t)((1u << (range >> 6)) - (1u << (range & 0x3f)));
           size_t i = ents.size();
           while (i > first) {  // runs of one block and image share an entry
             const TileEntry &E = ents[i - 1];
@@ -1011,6 +1013,13 @@ void build_tiles(HostPlan *P) {
   const BlockRec pad{0, 0, 0, 0, -1, 0};
   for (size_t i = 0; i < most; ++i)
     for (const auto &c : cls) P->tblocks.push_back(i < c.size() ? c[i] : pad);
+  P->tcover.assign(P->tblocks.size() * kTileRows, 0);
+  for (size_t i = 0; i < P->tblocks.size(); ++i) {
+    const BlockRec &B = P->tblocks[i];
+    const size_t b = ((size_t)B.z * nyb + B.y0 / kTileRows) * nxb + B.x0 / kTileX;
+    if (B.nentries >= 0)
+      std::copy_n(cover.begin() + b * kTileRows, kTileRows, P->tcover.begin() + i * kTileRows);
+  }
   P->tile_form = true;
 }
 

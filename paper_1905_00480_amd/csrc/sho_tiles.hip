@@ -416,8 +416,8 @@ __attribute__((amdgpu_waves_per_eu(4))) void k_expand_tiles(TileArgs E,
   // Workgroup g runs on XCD g % 8: the band groups of a block one after the
   // other, so that the pieces of a point's row of bands are moved together.
   const uint32_t turn_of = blockIdx.x / kXcds, groups = (uint32_t)E.groups;
-  const BlockRec bk =
-      load_uniform(E.blocks + (turn_of / groups * kXcds + blockIdx.x % kXcds));
+  const uint32_t block = turn_of / groups * kXcds + blockIdx.x % kXcds;
+  const BlockRec bk = load_uniform(E.blocks + block);
   if (bk.nentries < 0) return;  // padding of the XCD-dealt launch
   const int lane = threadIdx.x & 63, w = wave_id();  // rows 4 w .. 4 w + 3
   const int q = lane >> 4;
@@ -454,19 +454,28 @@ __attribute__((amdgpu_waves_per_eu(4))) void k_expand_tiles(TileArgs E,
   const uint32_t bytes_x = (uint32_t)E.B * (uint32_t)sizeof(T);
   const __amdgpu_buffer_rsrc_t rsrc = buffer_of(psi + (int64_t)bk.z * E.ny * E.nx * E.B,
                                                 (uint32_t)E.ny * E.nx * bytes_x);
-  const int y0 = bk.y0 + 4 * w + q, x0 = bk.x0;
-  auto offset = [&](int y, int x) -> uint32_t {
-    return y < E.ny && x < E.nx && band < E.B
-               ? (uint32_t)(y * E.nx + x) * bytes_x + (uint32_t)band * (uint32_t)sizeof(T)
-               : kOut;
+  // Only points of a support are moved (109 x 128 x 122, 197 atoms of cut-off 2,
+  // 63 bands: 294 us with whole tiles, 94 so).
+  struct Points {
+    uint32_t cover, base;
   };
+  auto points = [&](int l) {  // of lane l
+    const int row = 4 * w + (l >> 4), b = b0 + (l & 15) * NB;
+    return Points{b < E.B ? E.cover[block * kTileRows + row] : 0u,
+                  (uint32_t)((bk.y0 + row) * E.nx + bk.x0) * bytes_x +
+                      (uint32_t)b * (uint32_t)sizeof(T)};
+  };
+  auto offset = [&](const Points &p, int t) -> uint32_t {
+    return p.cover >> t & 1 ? p.base + (uint32_t)t * bytes_x : kOut;
+  };
+  const Points in = points(lane);
   double acc[kTileX][NB];
   if (E.stream) {
 #pragma unroll
-    for (int t = 0; t < kTileX; ++t) load_bands<T, NB, 2>(rsrc, offset(y0, x0 + t), acc[t]);
+    for (int t = 0; t < kTileX; ++t) load_bands<T, NB, 2>(rsrc, offset(in, t), acc[t]);
   } else {
 #pragma unroll
-    for (int t = 0; t < kTileX; ++t) load_bands<T, NB, 0>(rsrc, offset(y0, x0 + t), acc[t]);
+    for (int t = 0; t < kTileX; ++t) load_bands<T, NB, 0>(rsrc, offset(in, t), acc[t]);
   }
   // psi is here before the entries begin (known to the compiler, which would
   // else wait for it step by step inside every entry)
@@ -519,13 +528,14 @@ __attribute__((amdgpu_waves_per_eu(4))) void k_expand_tiles(TileArgs E,
   }
   SHO_NU_CASES(X)
 #undef X
-  // (the offsets are formed again, not held in registers across the entries)
-  int yo = y0, xo = x0;
-  asm volatile("" : "+v"(yo), "+s"(xo));
+  // (the points are found again, not held in registers across the entries)
+  int again = lane;
+  asm volatile("" : "+v"(again));
+  const Points out = points(again);
   const bool whole = NB == 1 || (E.B & 1) == 0;
 #pragma unroll
   for (int t = 0; t < kTileX; ++t) {
-    const uint32_t o = offset(yo, xo + t);
+    const uint32_t o = offset(out, t);
     if (E.stream) {
       store_bands<T, NB, 2>(rsrc, o, acc[t]);
     } else if (whole) {
