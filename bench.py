@@ -38,7 +38,8 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0  # MI355X HBM3E, published
-KERNEL_SRC = os.path.join(ROOT, "paper_1905_00480_amd", "csrc", "sho_kernels.hip")
+KERNEL_SRC = [os.path.join(ROOT, "paper_1905_00480_amd", "csrc", f)
+              for f in ("sho_kernels.hip", "sho_planes.hip", "sho_tiles.hip")]
 TRAFFIC = os.path.join(ROOT, "profiles", "traffic.json")
 
 
@@ -85,8 +86,11 @@ def parse():
 
 
 def kernel_source_sha():
-    with open(KERNEL_SRC, "rb") as f:
-        return hashlib.sha256(f.read()).hexdigest()[:16]
+    h = hashlib.sha256()
+    for path in KERNEL_SRC:
+        with open(path, "rb") as f:
+            h.update(f.read())
+    return h.hexdigest()[:16]
 
 
 def measured_traffic(kind, workload="scale"):
@@ -108,12 +112,14 @@ def measured_traffic(kind, workload="scale"):
 # kernels that make up one launch of the kind; the first names the main
 # kernel, whose dispatch count is the number of launches.
 COUNTER_KINDS = {
-    "scale": {"project": [r"k_project(_any|_blocks)?<5\b", r"k_zpass<5>"],
-              "expand_z": [r"k_u2<5>"],
-              "expand_xy": [r"k_expand_blocks<5, false>"]},
-    "batching": {"project": [r"k_project(_any|_blocks)?<9\b", r"k_zpass<[0-9]>"],
-                 "expand_z": [r"k_u2<9>", r"k_u2<[0-8]>"],
-                 "expand_xy": [r"k_expand_blocks<9, false>"]},
+    "scale": {"project": [r"k_project(_any|_blocks)?<5\b|k_project_planes<double, 5\b",
+                          r"k_zpass<5>|k_zpass_all<double, 5\b"],
+              "expand_z": [r"k_u2<5>|k_partials<double, 5\b"],
+              "expand_xy": [r"k_expand_blocks<5, false>|k_expand_tiles<double, 5\b"]},
+    "batching": {"project": [r"k_project(_any|_blocks)?<9\b|k_project_planes<double, 9\b",
+                             r"k_zpass<[0-9]>|k_zpass_all<double, 9\b"],
+                 "expand_z": [r"k_u2<9>|k_partials<double, 9\b", r"k_u2<[0-8]>"],
+                 "expand_xy": [r"k_expand_blocks<9, false>|k_expand_tiles<double, 9\b"]},
 }
 
 
@@ -134,7 +140,7 @@ def digest_counters(fetch_csv, write_csv, out=TRAFFIC):
                 if r["Counter_Name"] == counter:
                     rows.append((int(r["Dispatch_Id"]), r["Kernel_Name"],
                                  float(r["Counter_Value"]) * 1024.0))
-        first9 = min([d for d, k, _ in rows if re.search(r"k_(project\w*|expand_blocks)<9", k)]
+        first9 = min([d for d, k, _ in rows if re.search(r"k_(project\w*|expand_blocks)<(double, )?9", k)]
                      or [1 << 62])
         tot, cnt = {}, {}
         for d, k, v in rows:
