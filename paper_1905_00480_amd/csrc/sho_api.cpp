@@ -740,6 +740,10 @@ hipError_t run_expand(sho_plan_s *p, const void *c_v, void *psi_v, hipStream_t s
       });
     return e;
   }
+  // no tables of the named form would be a launch of nothing
+  if ((p->hp.expand_mode == sho::kExpandBlocks || p->hp.expand_mode == sho::kExpandOwner) &&
+      p->hp.blocks.empty() && !p->hp.lines.empty())
+    return hipErrorInvalidValue;
   if (p->fp32) {
     // FP32 plans: plane partials and the block form only
     sho::EArgs E = make_eargs(p);
@@ -1490,7 +1494,8 @@ sho_status sho_plan_set_expand(sho_plan_t p, int32_t mode, int32_t block_rows,
     return fail(SHO_E_INVALID, "deterministic plans expand in the owner form only");
   // a mode without a shape is the default again, which may run as tiles
   const bool det = (p->hp.flags & SHO_FLAG_DETERMINISTIC) != 0;
-  if (block_rows == 0 && block_x == 0 && !p->hp.tblocks.empty() && p->hp.expand_tbe_shift < 0 &&
+  if (block_rows == 0 && block_x == 0 && !p->hp.tblocks.empty() &&
+      (det || p->hp.expand_tbe_shift < 0) &&
       mode == (det ? sho::kExpandOwner : sho::kExpandBlocks)) {
     int32_t R = sho::owner_rows(p->hp), X = 32;
     if (!det) sho::default_block_shape(p->hp, &R, &X);
@@ -1562,7 +1567,7 @@ sho_status sho_plan_set_expand_tile(sho_plan_t p, int32_t band_tile) {
     if (e != hipSuccess) return hip_fail(e, "hipDeviceSynchronize");
   }
   p->hp.expand_tbe_shift = tbs;
-  p->hp.tile_form = false;
+  // the other forms do not use it (deterministic plans keep their tiles)
   if (p->hp.expand_mode == sho::kExpandBlocks && tbs < 0 && !p->hp.tblocks.empty()) {
     // the default tile again: the default form
     sho::default_block_shape(p->hp, &p->hp.blk_rows, &p->hp.blk_x);
@@ -1571,6 +1576,7 @@ sho_status sho_plan_set_expand_tile(sho_plan_t p, int32_t band_tile) {
     int32_t R = 0, X = 0;
     sho::default_block_shape(p->hp, &R, &X);
     sho::build_blocks(&p->hp, R, X);
+    p->hp.tile_form = false;
     if (dev) {
       hipError_t e = upload_blocks(p);
       if (e != hipSuccess) return hip_fail(e, "block upload");

@@ -1,0 +1,53 @@
+"""Settings of a plan's forms on the GPU: whatever was set, the results are the
+oracle's, |x - x_oracle| <= 1e-12 A (A: the oracle's abs-sum of the entry)."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_1905_00480_amd import workloads as wl
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+RTOL = 1e-12
+
+
+def _bd():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1905_00480_amd import binding
+    binding.load_library()
+    return binding
+
+
+def _dev(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).to("cuda")
+
+
+def _check(t, ref, ab, what):
+    torch.cuda.synchronize()
+    err = np.abs(t.cpu().numpy().ravel() - ref.ravel())
+    bound = RTOL * ab.ravel() + 1e-300
+    assert np.all(err <= bound), "%s: %d entries off, max |d| %.3e" % (
+        what, int((err > bound).sum()), float(err.max()))
+
+
+@pytest.mark.parametrize("tile", [0, 8, 32])
+def test_deterministic_expansion_after_the_band_tile_is_set(tile):
+    bd = _bd()
+    s = wl.small_mixed()
+    psi, w = wl.psi_for(s), wl.coeffs_for(s)
+    d_psi, d_w = _dev(psi), _dev(w)
+    ref, ab = oracle.expand(*s.geometry(), w, psi, with_abs=True)
+    plan = bd.Plan.from_system(s, flags=bd.FLAG_DETERMINISTIC)
+    first = plan.expand(d_w, d_psi.clone())
+    plan.set_expand_tile(tile)
+    again = plan.expand(d_w, d_psi.clone())
+    _check(again, ref, ab, "band tile %d" % tile)
+    assert torch.equal(first, again)
+    plan.set_expand(bd.EXPAND_OWNER, 0, 16)  # a form of its own, then the tile
+    plan.set_expand_tile(tile)
+    _check(plan.expand(d_w, d_psi.clone()), ref, ab, "owner form, band tile %d" % tile)
+    plan.set_expand(bd.EXPAND_OWNER)
+    assert torch.equal(first, plan.expand(d_w, d_psi.clone()))
+    plan.close()
