@@ -312,8 +312,10 @@ __device__ inline void add_entry(const TileArgs &E, uint32_t range, uint32_t ste
                      (4 * w + i4) * nfp + q;
   const Bands<T, NB> *ut = reinterpret_cast<const Bands<T, NB> *>(
       slot + (kXRows + kYRows) * table_nfp_c(NUMAX) * 8);
-  // four ny of one nx: quarter q reads pair q, or the last one there is (its
-  // factor is zero) where fewer are left
+  // four ny of one nx: quarter q reads pair q; where fewer are left, it reads
+  // the last one there is and takes zero instead (the value itself: a zero
+  // factor would make NaN of an infinite partial; the table's value is finite
+  // in the rows that exist)
   const Bands<T, NB> *um[4];
 #pragma unroll
   for (int m = 0; m < 4; ++m) um[m] = ut + min(q, m) * 16 + (lane & 15);
@@ -332,9 +334,10 @@ __device__ inline void add_entry(const TileArgs &E, uint32_t range, uint32_t ste
       const int left = NU - nx - 4 * g;  // functions after the group's first
       const int m = left < 3 ? left : 3;
       const Bands<T, NB> u = um[m][(p + 4 * g) * 16];
-      const double a = m == 3 || q <= m ? ay[g] : 0.0;
+      const bool there = m == 3 || q <= m;
 #pragma unroll
-      for (int h = 0; h < NB; ++h) U[nx][h] = mfma4(a, (double)u.v[h], U[nx][h]);
+      for (int h = 0; h < NB; ++h)
+        U[nx][h] = mfma4(ay[g], there ? (double)u.v[h] : 0.0, U[nx][h]);
     }
     p += NF - nx;
   }
