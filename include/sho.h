@@ -116,15 +116,18 @@ typedef int32_t sho_status;
                                              overlapping atoms, over band
                                              tiles) is taken in an order fixed
                                              by the plan, never through
-                                             atomics.  The projection and the
-                                             derivative keep one coefficient
-                                             tile per wave, added in wave
-                                             order, and one work item per
-                                             atom; the expansion runs as
-                                             tiles or in the owner form
+                                             atomics.  The projection adds
+                                             plane sums in the plan's order
+                                             or, like the derivative, keeps
+                                             one coefficient tile per wave,
+                                             added in wave order, and one work
+                                             item per atom; the expansion runs
+                                             as tiles or in the owner form
                                              (SHO_EXPAND_OWNER), both ordered.
                                              Repeated calls on the same inputs
-                                             give identical bits.  FP64 only;
+                                             give identical bits, captured or
+                                             not, until the plan's settings
+                                             change.  FP64 only;
                                              not with SHO_FLAG_STORED,
                                              SHO_FLAG_PER_ATOM or
                                              SHO_FLAG_FP32 (SHO_E_INVALID). */
@@ -310,7 +313,8 @@ sho_status sho_plan_set_centres(sho_plan_t plan, const double *pos,
  * tuned the library may take the projection plane by plane of the atoms, with
  * the plane sums in the plan's device scratch (allocated by the first call
  * that needs it); on a stream that the caller is capturing, and where the
- * scratch cannot be allocated, it runs the work items, which use none. */
+ * scratch cannot be allocated, it runs the work items, which use none, or, in
+ * deterministic plans, the same sums in the same order without scratch. */
 sho_status sho_plan_project(sho_plan_t plan, const double *psi, double *c,
                             void *stream);
 

@@ -99,6 +99,7 @@ struct sho_plan_s {
   double *d_tile_phase = nullptr;        // Bloch plans: (cos, sin) per entry
   sho::PlaneUnit *d_punits = nullptr;    // plane form of the projection
   sho::PlaneBundle *d_pbundles = nullptr;
+  int32_t *d_plane_unit = nullptr;
   double *d_plane_phase = nullptr;       // Bloch plans: (cos, sin) per bundle
   sho::EntryRec *d_entries = nullptr;
   uint32_t *d_run_desc = nullptr;
@@ -142,8 +143,10 @@ void free_plan_device(sho_plan_s *p) {
   p->d_tcover = nullptr;
   if (p->d_punits) (void)hipFree(p->d_punits);
   if (p->d_pbundles) (void)hipFree(p->d_pbundles);
+  if (p->d_plane_unit) (void)hipFree(p->d_plane_unit);
   p->d_punits = nullptr;
   p->d_pbundles = nullptr;
+  p->d_plane_unit = nullptr;
   if (p->scratch_ev) (void)hipEventDestroy(p->scratch_ev);
   p->scratch_ev = nullptr;
   if (p->d_atoms) (void)hipFree(p->d_atoms);
@@ -365,6 +368,7 @@ sho::PlaneArgs make_plane_args(const sho_plan_s *p) {
   A.u2_off = p->d_u2_off;
   A.nu_atoms = p->d_nu_atoms;
   A.phase = p->bloch ? p->d_plane_phase : nullptr;
+  A.plane_unit = p->hp.plane_unit.empty() ? nullptr : p->d_plane_unit;
   A.nunits = (int32_t)p->hp.punits.size();
   A.natoms_u2 = (int32_t)p->hp.nu_atoms.size();
   A.nx = p->hp.grid.n[0];
@@ -536,6 +540,7 @@ int64_t estimate_device_bytes(const sho::HostPlan &hp) {
               b((int64_t)hp.run_desc.size(), 4) +
               b((int64_t)hp.punits.size(), sizeof(sho::PlaneUnit)) +
               b((int64_t)hp.pbundles.size(), sizeof(sho::PlaneBundle)) +
+              b((int64_t)hp.plane_unit.size(), sizeof(int32_t)) +
               b((int64_t)hp.tblocks.size(), sizeof(sho::BlockRec)) +
               b((int64_t)hp.tentries.size(), sizeof(sho::TileEntry)) +
               b((int64_t)hp.tcover.size(), sizeof(uint16_t));
@@ -626,17 +631,24 @@ sho_status ensure_u2(sho_plan_s *p) {
   return SHO_OK;
 }
 
-// The projection's launches on s (arguments already checked); planes: in the
-// plane form, with its plane sums in the plan's scratch.
+// How a plan whose form is kProjectItems runs.
+enum class Items {
+  kWork,    // by work items
+  kPlanes,  // by planes, with the plane sums in the plan's scratch
+  kAtoms,   // the sums of kPlanes without scratch (deterministic plans)
+};
+
+// The projection's launches on s (arguments already checked).
 hipError_t run_project(sho_plan_s *p, const void *psi_v, void *c_v, hipStream_t s,
-                       bool prof, bool planes) {
+                       bool prof, Items how) {
   const double *psi = static_cast<const double *>(psi_v);
   double *c = static_cast<double *>(c_v);
   // atoms whose support missed the grid entirely keep zero coefficients;
   // atoms shared by several work items (and every stored point chunk) are
   // summed into zeroed coefficients
   const bool blocks = p->hp.proj_form == sho::kProjectBlocks;
-  bool zero = (p->hp.any_split && !blocks && !planes) || (p->hp.flags & SHO_FLAG_STORED);
+  bool zero = (p->hp.any_split && !blocks && how == Items::kWork) ||
+              (p->hp.flags & SHO_FLAG_STORED);
   for (const auto &A : p->hp.atoms) zero |= (A.npoints == 0);
   if (zero) {
     hipError_t e = sho::launch_fill(c, p->hp.coeff_rows * p->hp.nbands, 0.0, s);
@@ -653,10 +665,12 @@ hipError_t run_project(sho_plan_s *p, const void *psi_v, void *c_v, hipStream_t 
       return e1;
     });
   }
-  if (planes)
+  if (how != Items::kWork)
     return timed(p, prof, SHO_KERNEL_PROJECT, s, [&]() {
-      return sho::launch_project_planes(p->hp.nu_max, p->fp32, make_plane_args(p), psi_v,
-                                        p->d_u2, c_v, s);
+      return how == Items::kAtoms
+                 ? sho::launch_project_atoms(p->hp.nu_max, make_plane_args(p), psi, c, s)
+                 : sho::launch_project_planes(p->hp.nu_max, p->fp32, make_plane_args(p), psi_v,
+                                              p->d_u2, c_v, s);
     });
   return timed(p, prof, SHO_KERNEL_PROJECT, s, [&]() {
     if (p->hp.flags & SHO_FLAG_STORED) {
@@ -806,23 +820,29 @@ hipError_t run_expand(sho_plan_s *p, const void *c_v, void *psi_v, hipStream_t s
   return e;
 }
 
-// Whether the next projection takes the plane form (its scratch must be there).
+// Whether the next projection takes the plane form.
 bool uses_planes(const sho_plan_s *p) {
   return p->hp.plane_form && p->hp.proj_form == sho::kProjectItems;
 }
 
+// How it runs with the plan's scratch at hand.
+Items with_scratch(const sho_plan_s *p) { return uses_planes(p) ? Items::kPlanes : Items::kWork; }
+
 // run_project with the plane sums of the block or plane form in the plan's
-// own scratch, ordered against the scratch's other users (the item form uses
-// none).  The plane form gives way to the item form where its scratch may not
-// be used or had: on a stream that a caller is capturing (the captured work
-// could replay beside other calls of the plan) and when the allocation fails.
+// own scratch, ordered against the scratch's other users (the other forms use
+// none).  The plane form gives way where its scratch may not be used or had: on
+// a stream that a caller is capturing (the captured work could replay beside
+// other calls of the plan) and when the allocation fails.  Then work items run,
+// or, in deterministic plans, whose calls all give the same bits, the plane
+// form's sums without scratch.
 hipError_t run_project_own(sho_plan_s *p, const void *psi, void *c, hipStream_t s, bool prof) {
-  bool planes = uses_planes(p);
-  if (planes) planes = !capturing(s) && ensure_u2(p) == SHO_OK;
-  if (!planes && p->hp.proj_form != sho::kProjectBlocks)
-    return run_project(p, psi, c, s, prof, false);
+  Items how = with_scratch(p);
+  if (how == Items::kPlanes && (capturing(s) || ensure_u2(p) != SHO_OK))
+    how = (p->hp.flags & SHO_FLAG_DETERMINISTIC) ? Items::kAtoms : Items::kWork;
+  if (how != Items::kPlanes && p->hp.proj_form != sho::kProjectBlocks)
+    return run_project(p, psi, c, s, prof, how);
   hipError_t e = scratch_acquire(p, s);
-  if (e == hipSuccess) e = run_project(p, psi, c, s, prof, planes);
+  if (e == hipSuccess) e = run_project(p, psi, c, s, prof, how);
   if (e == hipSuccess) e = scratch_release(p, s);
   return e;
 }
@@ -891,6 +911,7 @@ sho_status finish_plan(sho_plan_s *p, uint32_t flags, int32_t nbands, bool f32,
       (e = upload(&p->d_tcover, p->hp.tcover, &p->device_bytes)) != hipSuccess ||
       (e = upload(&p->d_punits, p->hp.punits, &p->device_bytes)) != hipSuccess ||
       (e = upload(&p->d_pbundles, p->hp.pbundles, &p->device_bytes)) != hipSuccess ||
+      (e = upload(&p->d_plane_unit, p->hp.plane_unit, &p->device_bytes)) != hipSuccess ||
       (e = upload(&p->d_doff, p->hp.dmat_off, &p->device_bytes)) != hipSuccess ||
       (e = upload(&p->d_run_atom, p->hp.run_atom, &p->device_bytes)) != hipSuccess ||
       (e = upload(&p->d_row_runs, p->hp.row_runs, &p->device_bytes)) != hipSuccess ||
@@ -1717,11 +1738,11 @@ sho_status sho_plan_tune(sho_plan_t p, const void *psi, void *c, int32_t reps,
   hipError_t e = hipEventCreate(&ea);
   if (e == hipSuccess) e = hipEventCreate(&eb);
   auto time_current = [&](double *ms) -> hipError_t {
-    const bool planes = uses_planes(p);
-    hipError_t e1 = run_project(p, psi, c, s, false, planes);  // warm-up
+    const Items how = with_scratch(p);
+    hipError_t e1 = run_project(p, psi, c, s, false, how);  // warm-up
     if (e1 == hipSuccess) e1 = hipEventRecord(ea, s);
     for (int r = 0; r < reps && e1 == hipSuccess; ++r)
-      e1 = run_project(p, psi, c, s, false, planes);
+      e1 = run_project(p, psi, c, s, false, how);
     if (e1 == hipSuccess) e1 = hipEventRecord(eb, s);
     if (e1 == hipSuccess) e1 = hipEventSynchronize(eb);
     float t = 0.f;
@@ -1934,7 +1955,7 @@ sho_status sho_graph_create(sho_plan_t p, const double *psi, double *c, double *
     return fail(SHO_E_INVALID, "out and c overlap");
   if ((st = ensure_u2(p)) != SHO_OK) return st;
   return capture(p, [&](hipStream_t cs) {
-    hipError_t e1 = run_project(p, psi, c, cs, false, uses_planes(p));
+    hipError_t e1 = run_project(p, psi, c, cs, false, with_scratch(p));
     if (e1 == hipSuccess) e1 = run_expand(p, c, out, cs, false, p->d_u2);
     return e1;
   }, g);
@@ -1950,7 +1971,7 @@ sho_status sho_graph_create_apply(sho_plan_t p, const double *psi, const double 
   if (st != SHO_OK) return st;
   if ((st = ensure_u2(p)) != SHO_OK) return st;
   return capture(p, [&](hipStream_t cs) {
-    hipError_t e1 = run_project(p, psi, c, cs, false, uses_planes(p));
+    hipError_t e1 = run_project(p, psi, c, cs, false, with_scratch(p));
     if (e1 == hipSuccess) e1 = run_multiply(p, D, c, d, cs);
     if (e1 == hipSuccess) e1 = run_expand(p, d, out, cs, false, p->d_u2);
     return e1;

@@ -290,6 +290,7 @@ struct HostPlan {
   std::vector<PlaneUnit> punits;        // XCD-interleaved by memory plane
   std::vector<PlaneBundle> pbundles;
   std::vector<int32_t> pbundle_run;     // Bloch plans: the first run of each
+  std::vector<int32_t> plane_unit;      // deterministic plans: unit of every plane
   int32_t pblk_tb_shift = 0;            // log2(bands per lane slot), block form
   BlockSet pblk;                        // the projection's block form
   std::vector<int64_t> run_poff;      // stored projectors: first double of

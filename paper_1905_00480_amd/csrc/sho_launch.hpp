@@ -82,6 +82,7 @@ struct PlaneArgs {
                               // in units of u2_scale values
   const int32_t *nu_atoms;    // atoms with a support
   const double *phase;        // Bloch plans: (cos, sin) of k.T per bundle
+  const int32_t *plane_unit;  // deterministic plans: the unit of every plane
   int32_t nunits;
   int32_t natoms_u2;
   int32_t nx, ny;
@@ -221,6 +222,11 @@ hipError_t static_scratch(double **ptr);
 // float if f32, else double.
 hipError_t launch_project_planes(int nu_max, bool f32, const PlaneArgs &P, const void *psi,
                                  void *p2, void *c, hipStream_t s);
+
+// The same coefficients, bit for bit, without the plane sums in memory (FP64
+// plans with a plane_unit table).
+hipError_t launch_project_atoms(int nu_max, const PlaneArgs &P, const double *psi, double *c,
+                                hipStream_t s);
 
 // Tile form of the expansion: plane partials of c into u2 (pairs in nx-major
 // order, so not those of launch_expand_planes), then the blocks.  c, u2 and

@@ -488,6 +488,7 @@ void build_planes(HostPlan *P) {
   P->plane_lds_bundles = 0;
   P->punits.clear();
   P->pbundles.clear();
+  P->plane_unit.clear();
   if (P->flags & (SHO_FLAG_STORED | SHO_FLAG_PER_ATOM)) return;
   // a memory plane is addressed by 32-bit byte offsets, the tables of one
   // atom are staged in LDS
@@ -599,6 +600,15 @@ void build_planes(HostPlan *P) {
   } else {
     for (const Keyed &k : all) P->punits.push_back(k.u);
     while (P->punits.size() % kXcds) P->punits.push_back(pad);
+  }
+  if (P->flags & SHO_FLAG_DETERMINISTIC) {
+    // (the bundles were made plane by plane)
+    std::vector<int32_t> &pu = P->plane_unit;
+    for (size_t i = 0; i < P->punits.size(); ++i)
+      if (P->punits[i].nu >= 0) pu.push_back((int32_t)i);
+    std::sort(pu.begin(), pu.end(), [&](int32_t x, int32_t y) {
+      return P->punits[x].b0 < P->punits[y].b0;
+    });
   }
   // When the form runs.  One small atom: the item form's single launch is
   // faster (16^3, one atom of 2109 points, one band: 9.9 us against 15.3), and

@@ -110,18 +110,27 @@ __device__ inline double rotate(double v, double c, double sg) {
   return fma(sg, __shfl_xor(v, 1), c * v);
 }
 
-// NB: adjacent bands per lane (16 NB per wave).
-template <typename T, int NU, int NB>
+// The waves that share a unit: this one, how many, and this thread's place.
+struct Team {
+  int w, nw, thread;
+};
+
+// Adds up one plane.  Its sums, pair (nx, ny) at ny NF - ny (ny - 1) / 2 + nx, go
+// to the plane's place in the plane sums p2, or (kLds) to p2 in LDS, 16 bands per
+// pair.  NB: adjacent bands per lane (16 NB per wave).  The barriers are the
+// workgroup's: one, with several waves to a team three, also for a unit without
+// bundles.
+template <typename T, int NU, int NB, bool kLds>
 __device__ inline void project_plane(const PlaneArgs &P, const PlaneUnit &U, int group,
-                                     const T *__restrict__ psi, T *__restrict__ p2,
-                                     char *lds) {
+                                     const T *__restrict__ psi, T *__restrict__ p2, char *lds,
+                                     const Team &team) {
   constexpr int NF = NU + 1;
   constexpr int NG = pair_groups(NU);
   constexpr int S = (NF + 3) / 4;  // groups of four functions
   constexpr int W = 4 * S;         // table row in LDS
   constexpr bool kDeep = NB == 1 || NU <= 7;
   const int lane = threadIdx.x & 63;
-  const int w = wave_id(), nw = (int)blockDim.x >> 6;
+  const int w = team.w, nw = team.nw;
   const int q = lane >> 4, i4 = lane & 3;
   const int band = (group * 16 + (lane & 15)) * NB;
   const int nfp = U.nfp;
@@ -137,22 +146,23 @@ __device__ inline void project_plane(const PlaneArgs &P, const PlaneUnit &U, int
     const int nt = ((U.mx + 3) & ~3) * W;
     const int4 *src = reinterpret_cast<const int4 *>(P.bundles + U.b0);
     constexpr int K = 6;  // loads in flight per lane
-    for (int t0 = threadIdx.x; t0 < max(nt, 3 * nb); t0 += K * blockDim.x) {
+    const int threads = nw * 64;
+    for (int t0 = team.thread; t0 < max(nt, 3 * nb); t0 += K * threads) {
       double v[K];
       int4 c = make_int4(0, 0, 0, 0);
 #pragma unroll
       for (int u = 0; u < K; ++u) {
-        const int t = t0 + u * blockDim.x, x = t / W, n = t % W;
+        const int t = t0 + u * threads, x = t / W, n = t % W;
         v[u] = x < U.mx ? gx[x * nfp + n] : 0.0;
       }
       if (t0 < 3 * nb) c = src[t0];
 #pragma unroll
       for (int u = 0; u < K; ++u)
-        if (t0 + u * (int)blockDim.x < nt) tab[t0 + u * blockDim.x] = v[u];
+        if (t0 + u * threads < nt) tab[t0 + u * threads] = v[u];
       if (t0 < 3 * nb) reinterpret_cast<int4 *>(bun)[t0] = c;
 #pragma unroll
       for (int u = 1; u < K; ++u) {
-        const int t = t0 + u * blockDim.x;
+        const int t = t0 + u * threads;
         if (t < 3 * nb) reinterpret_cast<int4 *>(bun)[t] = src[t];
       }
     }
@@ -341,9 +351,8 @@ __device__ inline void project_plane(const PlaneArgs &P, const PlaneUnit &U, int
       for (int k = 0; k < NG; ++k) red[((w * NB + h) * NG + k) * 64 + lane] = T2[h][k];
     __syncthreads();
   }
-  // plane sums, pair (nx, ny) at ny NF - ny (ny - 1) / 2 + nx
-  T *dst = p2 + U.sums * P.B + band;
-  const bool pairs = NB == 2 && (P.B & 1) == 0;  // (the scratch is aligned)
+  T *dst = p2 + (kLds ? (int64_t)(lane & 15) : U.sums * P.B + band);
+  const bool pairs = !kLds && NB == 2 && (P.B & 1) == 0;  // (the scratch is aligned)
   int k = 0;
 #pragma unroll
   for (int nx = 0; nx < NF; ++nx) {
@@ -361,8 +370,12 @@ __device__ inline void project_plane(const PlaneArgs &P, const PlaneUnit &U, int
       }
       const int ny = 4 * g + q;
       const int pair = ny * NF - ny * (ny - 1) / 2 + nx;
-      T *o = dst + (int64_t)pair * P.B;
+      T *o = dst + (kLds ? (int64_t)16 * pair : (int64_t)pair * P.B);
       if (ny > NU - nx) continue;
+      if constexpr (kLds) {
+        *o = (T)sum[0];
+        continue;
+      }
       if constexpr (NB == 2) {
         if (pairs && band < P.B) {
           struct __attribute__((aligned(2 * sizeof(T)))) T2v {
@@ -394,10 +407,12 @@ __attribute__((amdgpu_waves_per_eu(waves(NUMAX, NB)))) void k_project_planes(
   extern __shared__ double lds[];
   const PlaneUnit U = load_uniform(P.units + blockIdx.x);
   if (U.nu < 0) return;  // padding of the XCD-dealt launch
+  const Team team{wave_id(), (int)blockDim.x >> 6, (int)threadIdx.x};
   switch (U.nu) {
 #define X(N)                                                                                  \
   case N:                                                                                     \
-    if constexpr (N <= NUMAX) project_plane<T, N, NB>(P, U, blockIdx.y, psi, p2, (char *)lds); \
+    if constexpr (N <= NUMAX)                                                                 \
+      project_plane<T, N, NB, false>(P, U, blockIdx.y, psi, p2, (char *)lds, team);           \
     break;
     SHO_NU_CASES(X)
 #undef X
@@ -486,15 +501,106 @@ __global__ __launch_bounds__(kZThreads) void k_zpass_all(PlaneArgs P, const T *_
   }
 }
 
+// The same sums without scratch, to the last bit: one workgroup per (atom, 16
+// bands), whose teams (the waves of a unit each) take the atom's planes in turn;
+// their sums meet in LDS and are added to the coefficients there in the order of
+// k_zpass_all.  For deterministic plans where the plane sums may not be used or
+// had, so that a call gives the same bits there.  Bound by the latency of a
+// team's planes: 128^3, 512 atoms, cut-off 5, 32 bands 329 us (work items of the
+// mode 336, plane sums in memory 190); 64^3, 120 atoms, cut-off 9, 64 bands 648
+// (2770, 395); 8 uneven atoms, 6 bands 121 (132, 20); 96^3, 300 atoms, cut-off 3,
+// 20 bands 141 (118, 53).
+struct AtomLds {
+  int team, sums, coeff;  // bytes of a team's part, begin of the others
+};
+
+template <int NU>
+__device__ inline void project_atom(const PlaneArgs &P, const AtomRec &A, const AtomLds &at,
+                                    const double *__restrict__ psi, double *__restrict__ c,
+                                    char *lds) {
+  constexpr int NF = NU + 1;
+  constexpr int NS = NF * (NF + 1) * (NF + 2) / 6;
+  constexpr int NP = NF * (NF + 1) / 2;
+  const int nw = P.waves, own = wave_id() / nw, teams = (int)blockDim.x / (64 * nw);
+  const Team team{wave_id() % nw, nw, (int)threadIdx.x - own * nw * 64};
+  double *sums = reinterpret_cast<double *>(lds + at.sums);  // [team][pair][16 bands]
+  double *acc = reinterpret_cast<double *>(lds + at.coeff);  // [row][16 bands]
+  const cptr<double> tz = as_const(P.tab) + A.tab_off + (int64_t)(A.mx + A.my) * A.tab_nfp;
+  // every coefficient is one thread's: item = (pair, band), all nz
+  auto rows = [&](int item, auto &&f) {  // f(nz, coefficient row) of the pair
+    const int p = item >> 4;
+    int ny = 0, nx = p;  // pair p -> (nx, ny), ny outer
+    while (nx >= NF - ny) {
+      nx -= NF - ny;
+      ++ny;
+    }
+    int base = 0;  // row of (nx, ny, nz): nz-major, then ny, nx fastest
+#pragma unroll 1
+    for (int nz = 0; nz <= NU - nx - ny; ++nz) {
+      const int m = NF - nz;  // functions nx of row ny = 0 in this layer
+      f(nz, base + ny * m - ny * (ny - 1) / 2 + nx);
+      base += m * (m + 1) / 2;
+    }
+  };
+  for (int t = threadIdx.x; t < NS * 16; t += blockDim.x) acc[t] = 0.0;
+  for (int j0 = 0; j0 < A.mz; j0 += teams) {
+    PlaneUnit U{};  // (no bundles: past the last plane)
+    if (j0 + own < A.mz) U = load_uniform(P.units + P.plane_unit[A.plane_begin + j0 + own]);
+    project_plane<double, NU, 1, true>(P, U, blockIdx.y, psi,
+                                       sums + own * NP * 16, lds + own * at.team, team);
+    __syncthreads();
+    const int n = min(teams, A.mz - j0);
+    for (int t = threadIdx.x; t < NP * 16; t += blockDim.x)
+      rows(t, [&](int nz, int row) {
+        double &a = acc[row * 16 + (t & 15)];
+        double v = a;
+        for (int i = 0; i < n; ++i)
+          v = fma(tz[(j0 + i) * A.tab_nfp + nz], sums[i * NP * 16 + t], v);
+        a = v;
+      });
+  }
+  for (int t = threadIdx.x; t < NP * 16; t += blockDim.x)
+    rows(t, [&](int nz, int row) {
+      const int band = (int)blockIdx.y * 16 + (t & 15);
+      double v = acc[row * 16 + (t & 15)];
+      // (the z pass fills its last round of planes up with zeros, which may turn
+      // the sign of a zero)
+      if (A.mz % kZ) v = fma(tz[(A.mz - 1) * A.tab_nfp + nz], 0.0, v);
+      if (band < P.B) c[(A.coeff_row + row) * P.B + band] = P.h3 * v;
+    });
+}
+
+constexpr int atom_threads(int numax) { return numax <= 7 ? 1024 : 512; }  // (registers)
+
+template <int NUMAX>
+__global__ __launch_bounds__(atom_threads(NUMAX)) void k_project_atoms(
+    PlaneArgs P, AtomLds at, const double *__restrict__ psi, double *__restrict__ c) {
+  extern __shared__ double lds[];
+  const AtomRec A = load_uniform(P.atoms + P.nu_atoms[blockIdx.x]);
+  switch (A.nu) {
+#define X(N)                                                                   \
+  case N:                                                                      \
+    if constexpr (N <= NUMAX) project_atom<N>(P, A, at, psi, c, (char *)lds); \
+    break;
+    SHO_NU_CASES(X)
+#undef X
+  }
+}
+
+// LDS of a unit: tables and bundles, then (over them) its waves' sums.
+template <int NUMAX>
+static size_t unit_lds(const PlaneArgs &P, int nb) {
+  constexpr int W = (NUMAX + 4) / 4 * 4;
+  return std::max(
+      (size_t)P.lds_rows * W * sizeof(double) + (size_t)P.lds_bundles * sizeof(PlaneBundle),
+      P.waves > 1 ? (size_t)P.waves * nb * pair_groups(NUMAX) * 64 * sizeof(double) : 0);
+}
+
 template <typename T, int NUMAX>
 static hipError_t launch_any(const PlaneArgs &P, const void *psi, void *p2, void *c,
                              hipStream_t s) {
   const dim3 g((unsigned)P.nunits, (unsigned)((P.B + 16 * P.nb - 1) / (16 * P.nb)));
-  const int W = (NUMAX + 4) / 4 * 4;
-  const size_t shm =
-      std::max((size_t)P.lds_rows * W * sizeof(double) +
-                   (size_t)P.lds_bundles * sizeof(PlaneBundle),
-               P.waves > 1 ? (size_t)P.waves * P.nb * pair_groups(NUMAX) * 64 * sizeof(double) : 0);
+  const size_t shm = unit_lds<NUMAX>(P, P.nb);
   if (P.nb == 1)
     hipLaunchKernelGGL((k_project_planes<T, NUMAX, 1>), g, dim3(64u * P.waves), shm, s, P,
                        static_cast<const T *>(psi), static_cast<T *>(p2));
@@ -528,7 +634,33 @@ static hipError_t launch_t(int nu_max, const PlaneArgs &P, const void *psi, void
   return launch_any<T, 10>(P, psi, p2, c, s);
 }
 
+template <int NUMAX>
+static hipError_t launch_atoms(const PlaneArgs &P, const double *psi, double *c, hipStream_t s) {
+  constexpr size_t kLds = 160 * 1024;
+  const size_t pairs = (NUMAX + 1) * (NUMAX + 2) / 2, row = 16 * sizeof(double);
+  const size_t coeff = pairs * (NUMAX + 3) / 3 * row, team = unit_lds<NUMAX>(P, 1);
+  // as many teams as fit (one does: at most 42 + 8.3 + 35.8 KB at cut-off 10)
+  const int teams = (int)std::min<size_t>(atom_threads(NUMAX) / (64 * P.waves),
+                                          (kLds - coeff) / (team + pairs * row));
+  if (teams < 1) return hipErrorInvalidValue;
+  const AtomLds at{(int)team, (int)(teams * team), (int)(teams * (team + pairs * row))};
+  hipLaunchKernelGGL((k_project_atoms<NUMAX>), dim3((unsigned)P.natoms_u2, (unsigned)(P.B + 15) / 16),
+                     dim3(64u * P.waves * teams), at.coeff + coeff, s, P, at, psi, c);
+  return hipGetLastError();
+}
+
 }  // namespace planes
+
+hipError_t launch_project_atoms(int nu_max, const PlaneArgs &P, const double *psi, double *c,
+                                hipStream_t s) {
+  if (P.natoms_u2 <= 0) return hipSuccess;
+  if (!P.plane_unit) return hipErrorInvalidValue;
+  if (nu_max <= 3) return planes::launch_atoms<3>(P, psi, c, s);
+  if (nu_max <= 5) return planes::launch_atoms<5>(P, psi, c, s);
+  if (nu_max <= 7) return planes::launch_atoms<7>(P, psi, c, s);
+  if (nu_max <= 9) return planes::launch_atoms<9>(P, psi, c, s);
+  return planes::launch_atoms<10>(P, psi, c, s);
+}
 
 hipError_t launch_project_planes(int nu_max, bool f32, const PlaneArgs &P, const void *psi,
                                  void *p2, void *c, hipStream_t s) {
