@@ -434,8 +434,10 @@ sho_status sho_plan_profile_read(sho_plan_t plan, int64_t *counts,
  * band_tile bands share a lane slot (power of two <= 64, 0 keeps the current
  * tile).  Plans with several cut-offs start with SHO_SCHED_SINGLE, others
  * with SHO_SCHED_BY_NU, target_points 16384 and the widest tile that fits.
- * A schedule that is set is run: the plane-by-plane projection that the
- * library may choose by itself (sho_plan_project) is given up.
+ * The library may run the default schedule plane by plane instead
+ * (sho_plan_project); any other schedule that is set runs as work items.
+ * Setting the values in force changes nothing, and the default ones bring
+ * the default form back.
  * set_schedule waits for the device (the work tables are replaced);
  * graphs made before it must be made again (sho_graph_launch refuses them).
  */
@@ -484,10 +486,12 @@ sho_status sho_plan_get_project(sho_plan_t plan, int32_t *form, int32_t *block_r
  *              atomics, so the result is bitwise reproducible (the form of
  *              SHO_FLAG_DETERMINISTIC plans, which accept no other).
  * All read and write every touched value of psi once with plain loads and
- * stores.  The default of mode 1 (2 for deterministic plans) without a shape
- * runs as tiles of 16 rows x 16 points whose sums stay in registers, in the
- * plan's order and without atomics, wherever that was measured to be faster;
- * a shape, or a band tile, picks the named form itself.  For SHO_FLAG_STORED plans the forms are: 0 the atom-owner form
+ * stores.  The default of mode 1 (2 for deterministic plans), with its default
+ * shape and band tile, runs as tiles of 16 rows x 16 points whose sums stay in
+ * registers, in the plan's order and without atomics, wherever that was
+ * measured to be faster; any other shape or band tile picks the named form
+ * itself.  Setting the values in force changes nothing.  For SHO_FLAG_STORED
+ * plans the forms are: 0 the atom-owner form
  * (global atomics, default for nu_max > 2), 1 the block form with the
  * products on matrix cores (default for nu_max <= 2).  block_rows = block_x = 0 picks the default shape; a shape whose
  * tile (rows x points x bands per tile: 8, 16, 32 or 64, the power of two
@@ -511,6 +515,18 @@ sho_status sho_plan_get_expand(sho_plan_t plan, int32_t *mode, int32_t *block_ro
  */
 sho_status sho_plan_set_expand_tile(sho_plan_t plan, int32_t band_tile);
 sho_status sho_plan_get_expand_tile(sho_plan_t plan, int32_t *band_tile);
+
+/*
+ * The forms that the next calls run with the plan's present settings:
+ * *project  SHO_PROJECT_ITEMS, SHO_PROJECT_BLOCKS or SHO_FORM_PLANES (the
+ *           default schedule plane by plane, *waves wavefronts to an atom
+ *           plane: 1, 2 or 4; 0 in the other forms);
+ * *expand   SHO_EXPAND_ROWS, _BLOCKS, _OWNER or SHO_FORM_TILES.
+ */
+#define SHO_FORM_PLANES 2
+#define SHO_FORM_TILES 3
+sho_status sho_plan_get_forms(sho_plan_t plan, int32_t *project, int32_t *waves,
+                              int32_t *expand);
 
 typedef struct sho_tune_expand_result {
   int32_t mode;          /* chosen SHO_EXPAND_* */

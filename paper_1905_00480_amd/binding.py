@@ -47,6 +47,7 @@ SCHED_XCD = 4
 EXPAND_ROWS = 0
 EXPAND_BLOCKS = 1
 EXPAND_OWNER = 2
+FORM_PLANES, FORM_TILES = 2, 3  # what sho_plan_get_forms adds to the above
 SCHEDULES = (SCHED_BY_NU, SCHED_SINGLE, SCHED_SINGLE_LPT, SCHED_SWEEP,
              SCHED_BY_NU | SCHED_XCD, SCHED_SINGLE | SCHED_XCD, SCHED_SINGLE_LPT | SCHED_XCD,
              SCHED_SWEEP | SCHED_XCD)
@@ -63,7 +64,7 @@ EXPORTS = (
     "sho_plan_set_expand_tile", "sho_plan_get_expand_tile", "sho_plan_tune_expand",
     "sho_cache_clear", "sho_plan_profile", "sho_plan_profile_read",
     "sho_plan_set_schedule", "sho_plan_get_schedule", "sho_plan_tune",
-    "sho_plan_set_expand", "sho_plan_get_expand",
+    "sho_plan_set_expand", "sho_plan_get_expand", "sho_plan_get_forms",
     "sho_plan_matrix_offsets", "sho_plan_multiply", "sho_plan_apply",
     "sho_graph_create_apply",
     "sho_graph_create", "sho_graph_launch", "sho_graph_destroy",
@@ -190,6 +191,7 @@ def load_library(path=None):
     lib.sho_plan_get_schedule.argtypes = [P, _i32p, _i32p, _i64p]
     lib.sho_plan_set_expand.argtypes = [P, ctypes.c_int32, ctypes.c_int32, ctypes.c_int32]
     lib.sho_plan_get_expand.argtypes = [P, _i32p, _i32p, _i32p]
+    lib.sho_plan_get_forms.argtypes = [P, _i32p, _i32p, _i32p]
     lib.sho_plan_tune.argtypes = [P, _vp, _vp, ctypes.c_int32, _vp,
                                   ctypes.POINTER(sho_tune_result)]
     lib.sho_graph_create.argtypes = [P, _vp, _vp, _vp, ctypes.POINTER(_vp)]
@@ -496,6 +498,13 @@ class Plan:
         _check(self._lib.sho_plan_get_expand(self._h, ctypes.byref(m), ctypes.byref(r),
                                              ctypes.byref(x)))
         return m.value, r.value, x.value
+
+    def forms(self):
+        """(project, waves, expand): the forms that the next calls run
+        (PROJECT_* or FORM_PLANES with its waves, EXPAND_* or FORM_TILES)."""
+        v = [ctypes.c_int32() for _ in range(3)]
+        _check(self._lib.sho_plan_get_forms(self._h, *[ctypes.byref(x) for x in v]))
+        return tuple(x.value for x in v)
 
     def set_expand_tile(self, band_tile):
         """Band tile of the expansion's block form (8..64, 0: default)."""

@@ -1426,8 +1426,12 @@ sho_status sho_plan_set_schedule(sho_plan_t p, int32_t schedule, int32_t band_ti
     hipError_t e = hipDeviceSynchronize();  // tables may be in use
     if (e != hipSuccess) return hip_fail(e, "hipDeviceSynchronize");
   }
+  // the values in force change nothing, the default ones bring the default
+  // form back, any others run as work items
+  if (schedule != p->hp.sched || tbs != p->hp.tb_shift || target_points != p->hp.target_points)
+    p->hp.plane_form = p->hp.plane_rule && schedule == p->hp.sched0 &&
+                       tbs == p->hp.tb_shift0 && target_points == p->hp.target_points0;
   sho::build_work(&p->hp, tbs, target_points, schedule);
-  p->hp.plane_form = false;  // the caller's schedule of work items runs
   if (p->hp.flags & SHO_FLAG_HOST_ONLY) return SHO_OK;
   hipError_t e = upload_schedule(p);
   if (e != hipSuccess) return hip_fail(e, "schedule upload");
@@ -1513,19 +1517,28 @@ sho_status sho_plan_set_expand(sho_plan_t p, int32_t mode, int32_t block_rows,
     return fail(SHO_E_INVALID, "stored plans expand in the row or block form");
   if ((p->hp.flags & SHO_FLAG_DETERMINISTIC) && mode != sho::kExpandOwner)
     return fail(SHO_E_INVALID, "deterministic plans expand in the owner form only");
-  // a mode without a shape is the default again, which may run as tiles
+  // the values in force change nothing
+  if (mode != sho::kExpandRows && mode == p->hp.expand_mode && block_rows == p->hp.blk_rows &&
+      block_x == p->hp.blk_x) {
+    p->sched_version++;
+    return SHO_OK;
+  }
+  // a mode without a shape, or with its default one, is the default again,
+  // which may run as tiles
   const bool det = (p->hp.flags & SHO_FLAG_DETERMINISTIC) != 0;
-  if (block_rows == 0 && block_x == 0 && !p->hp.tblocks.empty() &&
-      (det || p->hp.expand_tbe_shift < 0) &&
+  if (!p->hp.tblocks.empty() && (det || p->hp.expand_tbe_shift < 0) &&
       mode == (det ? sho::kExpandOwner : sho::kExpandBlocks)) {
     int32_t R = sho::owner_rows(p->hp), X = 32;
     if (!det) sho::default_block_shape(p->hp, &R, &X);
-    p->hp.blk_rows = R;
-    p->hp.blk_x = X;
-    p->hp.expand_mode = mode;
-    p->hp.tile_form = true;
-    p->sched_version++;
-    return SHO_OK;
+    const bool none = block_rows == 0 && block_x == 0;
+    if (none || (block_rows == R && block_x == X) || (det && block_rows == 0 && block_x == X)) {
+      p->hp.blk_rows = R;
+      p->hp.blk_x = X;
+      p->hp.expand_mode = mode;
+      p->hp.tile_form = true;
+      p->sched_version++;
+      return SHO_OK;
+    }
   }
   if (mode == sho::kExpandOwner) {
     const int32_t R = sho::owner_rows(p->hp);
@@ -1573,6 +1586,15 @@ sho_status sho_plan_get_expand(sho_plan_t p, int32_t *mode, int32_t *block_rows,
   return SHO_OK;
 }
 
+sho_status sho_plan_get_forms(sho_plan_t p, int32_t *project, int32_t *waves, int32_t *expand) {
+  if (!p || !project || !waves || !expand) return fail(SHO_E_INVALID, "NULL argument");
+  const bool planes = uses_planes(p);
+  *project = planes ? SHO_FORM_PLANES : p->hp.proj_form;
+  *waves = planes ? sho::plane_waves(p->hp) : 0;
+  *expand = p->hp.tile_form ? SHO_FORM_TILES : p->hp.expand_mode;
+  return SHO_OK;
+}
+
 sho_status sho_plan_set_expand_tile(sho_plan_t p, int32_t band_tile) {
   if (!p) return fail(SHO_E_INVALID, "NULL plan");
   if (p->hp.flags & SHO_FLAG_STORED)
@@ -1582,6 +1604,18 @@ sho_status sho_plan_set_expand_tile(sho_plan_t p, int32_t band_tile) {
     if ((1 << k) == band_tile) tbs = k;
   if (band_tile != 0 && tbs < 0)
     return fail(SHO_E_INVALID, "band_tile must be 0, 8, 16, 32 or 64");
+  // the values in force (with the tile's default shape, which it brings) change
+  // nothing; the default tile is the default, whether named or not
+  if (tbs >= 0 && tbs == sho::block_tile_shift(p->hp) &&
+      p->hp.expand_mode == sho::kExpandBlocks) {
+    int32_t R = 0, X = 0;
+    sho::default_block_shape(p->hp, &R, &X);
+    if (R == p->hp.blk_rows && X == p->hp.blk_x) {
+      p->sched_version++;
+      return SHO_OK;
+    }
+  }
+  if (tbs == sho::expand_tile_shift(p->hp.nbands, sho::kExpandBlocks)) tbs = -1;
   const bool dev = !(p->hp.flags & SHO_FLAG_HOST_ONLY);
   if (dev) {
     hipError_t e = hipDeviceSynchronize();

@@ -284,7 +284,10 @@ struct HostPlan {
                                                // every entry (as in EntryRec)
   std::vector<uint16_t> tcover;         // [tile][row]: bit x where a support is
   int32_t proj_form = 0;                // kProjectItems or kProjectBlocks
-  bool plane_form = false;              // item form's plan runs the plane form
+  bool plane_form = false;              // the item form runs by planes
+  bool plane_rule = false;              // so it does with the default schedule
+  int32_t sched0 = 0, tb_shift0 = 0;    // the default schedule
+  int64_t target_points0 = 0;
   int32_t plane_lds_rows = 0;           // x table rows of a unit, largest
   int32_t plane_lds_bundles = 0;        // bundles of a unit, largest
   std::vector<PlaneUnit> punits;        // XCD-interleaved by memory plane
@@ -431,8 +434,8 @@ inline int plane_waves(const HostPlan &P) {
 }
 
 // Work of the plane form of the projection (needs build_work for the order of
-// the runs): fills punits and pbundles, and sets plane_form if the form can and
-// should run.
+// the runs): fills punits and pbundles, sets plane_form if the form can and
+// should run, and takes the schedule as the default one.
 // Needs the offsets of the plane partials (build_rows) too.
 void build_planes(HostPlan *P);
 

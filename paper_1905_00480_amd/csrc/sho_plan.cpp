@@ -483,7 +483,10 @@ void build_work(HostPlan *P, int tb_shift, int64_t target_points, int32_t sched)
 }
 
 void build_planes(HostPlan *P) {
-  P->plane_form = false;
+  P->plane_form = P->plane_rule = false;
+  P->sched0 = P->sched;
+  P->tb_shift0 = P->tb_shift;
+  P->target_points0 = P->target_points;
   P->plane_lds_rows = 0;
   P->plane_lds_bundles = 0;
   P->punits.clear();
@@ -630,6 +633,7 @@ void build_planes(HostPlan *P) {
                                                         units >= 8192);
   P->plane_form = !((units <= 64 || bands <= 8) && largest <= 4096) && !many &&
                   !(f32 && P->support_points < 4 * P->union_points);
+  P->plane_rule = P->plane_form;
 }
 
 void build_stored(HostPlan *P, int32_t chunk) {

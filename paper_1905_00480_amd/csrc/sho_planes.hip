@@ -508,7 +508,7 @@ __global__ __launch_bounds__(kZThreads) void k_zpass_all(PlaneArgs P, const T *_
 // had, so that a call gives the same bits there.  Bound by the latency of a
 // team's planes: 128^3, 512 atoms, cut-off 5, 32 bands 329 us (work items of the
 // mode 336, plane sums in memory 190); 64^3, 120 atoms, cut-off 9, 64 bands 648
-// (2770, 395); 8 uneven atoms, 6 bands 121 (132, 20); 96^3, 300 atoms, cut-off 3,
+// (2770, 395); 8 uneven atoms, 20 bands 121 (132, 20); 96^3, 300 atoms, cut-off 3,
 // 20 bands 141 (118, 53).
 struct AtomLds {
   int team, sums, coeff;  // bytes of a team's part, begin of the others

@@ -51,3 +51,39 @@ def test_deterministic_expansion_after_the_band_tile_is_set(tile):
     plan.set_expand(bd.EXPAND_OWNER)
     assert torch.equal(first, plan.expand(d_w, d_psi.clone()))
     plan.close()
+
+
+@pytest.mark.parametrize("flags", ["f64", "det"])
+def test_results_through_a_round_trip_of_settings(flags):
+    """Each form that the settings name gives the oracle's results, and the
+    settings of a new plan, given back, its bits."""
+    bd = _bd()
+    fl = bd.FLAG_DETERMINISTIC if flags == "det" else 0
+    s = wl.small_mixed()
+    psi, w = wl.psi_for(s), wl.coeffs_for(s)
+    d_psi, d_w = _dev(psi), _dev(w)
+    refs = oracle.project(*s.geometry(), psi, with_abs=True)
+    exp = oracle.expand(*s.geometry(), w, psi, with_abs=True)
+    plan = bd.Plan.from_system(s, flags=fl)
+    forms, sc, tile, ex = plan.forms(), plan.schedule(), plan.expand_tile(), plan.expand_form()
+    c0, e0 = plan.project(d_psi).clone(), plan.expand(d_w, d_psi.clone())
+
+    def check(what):
+        _check(plan.project(d_psi), *refs, what)
+        _check(plan.expand(d_w, d_psi.clone()), *exp, what)
+
+    plan.set_schedule(bd.SCHED_SINGLE_LPT, 0, 4096)
+    plan.set_expand_tile(8)
+    plan.set_expand(*((ex[0], 0, 16) if fl else (ex[0], 4, 8)))
+    check("named forms")
+    plan.set_schedule(*sc)
+    plan.set_expand_tile(tile)
+    check("band tile back")
+    plan.set_expand(*ex)
+    assert plan.forms() == forms and plan.expand_form() == ex
+    assert torch.equal(plan.project(d_psi), c0)
+    e1 = plan.expand(d_w, d_psi.clone())
+    _check(e1, *exp, "all back")
+    if plan.forms()[2] == bd.FORM_TILES:  # (blocks add with atomics)
+        assert torch.equal(e0, e1)
+    plan.close()

@@ -68,3 +68,64 @@ def test_band_tile_leaves_deterministic_plans_their_form():
         p.set_expand_tile(tile)
         assert _info(p) == before
         p.close()
+
+
+def _state(p):
+    info = _info(p)
+    return (p.forms(), p.schedule(), p.expand_form(), p.expand_tile(), info["expand_blocks"],
+            info["expand_entries"])
+
+
+@pytest.mark.parametrize("kind", sorted(KINDS))
+def test_settings_survive_a_round_trip(kind):
+    """What the getters return, set again at once or after other settings, gives
+    the state that it was read in."""
+    stored = kind == "stored"
+    base = bd.SCHED_SINGLE if kind == "bloch" else bd.SCHED_SINGLE_LPT
+    p = _plan(KINDS[kind])
+    fresh = _state(p)
+    sc, ex, tile, pr = p.schedule(), p.expand_form(), p.expand_tile(), p.project_form()
+    if kind in ("f64", "det", "bloch"):
+        assert fresh[0] == (bd.FORM_PLANES, 4, bd.FORM_TILES)
+
+    def give_back():
+        p.set_schedule(*sc)
+        if not stored:
+            p.set_expand_tile(tile)
+        p.set_expand(*ex)
+        p.set_project(*pr)
+
+    give_back()
+    assert _state(p) == fresh
+    p.set_schedule(base, 0, 4096)
+    assert p.forms()[:2] == (bd.PROJECT_ITEMS, 0)
+    kept = _state(p)
+    p.set_schedule(*p.schedule())
+    assert _state(p) == kept
+    for tile2 in () if stored else (8, 16):
+        p.set_expand_tile(tile2)
+        kept = _state(p)
+        p.set_expand_tile(p.expand_tile())
+        assert _state(p) == kept
+    form = (bd.EXPAND_OWNER, 0, 16) if kind == "det" else (bd.EXPAND_BLOCKS, 2, 8)
+    p.set_expand(*form)
+    assert p.forms()[2] == form[0]
+    kept = _state(p)
+    p.set_expand(*p.expand_form())
+    assert _state(p) == kept
+    give_back()
+    if stored:  # (in the row form here, which takes no shape)
+        assert _state(p)[:2] == fresh[:2]
+    else:
+        assert _state(p) == fresh
+    p.close()
+
+
+def test_project_blocks_and_back():
+    p = _plan(0)
+    fresh = _state(p)
+    p.set_project(bd.PROJECT_BLOCKS)
+    assert p.forms()[0] == bd.PROJECT_BLOCKS
+    p.set_project(bd.PROJECT_ITEMS)
+    assert _state(p) == fresh
+    p.close()
