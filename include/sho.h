@@ -197,8 +197,9 @@ typedef struct sho_plan_info {
   int64_t stored_bytes;    /* of which stored projector tables */
   int64_t union_points;    /* distinct grid points covered by any support */
   int64_t expand_points;   /* grid points the expansion reads and writes:
-                              the tiles, the blocks (block form) or whole
-                              rows (row form) that some support touches */
+                              those of a support (tiles), the blocks (block
+                              form) or whole rows (row form) that some
+                              support touches */
   int64_t expand_scratch_doubles; /* plane partials of the expansion */
   int64_t expand_blocks;   /* workgroup blocks of the block-form expansion,
                               or its tiles where it runs as tiles */

@@ -1220,7 +1220,8 @@ sho_status sho_plan_get_info(sho_plan_t p, sho_plan_info *info) {
   info->union_points = p->hp.union_points;
   // the row kernel moves whole chunks of touched rows: with 32 or 64 bands
   // per tile a chunk spans 64 or 32 points (2048 doubles)
-  info->expand_points = p->hp.expand_mode != sho::kExpandRows
+  info->expand_points = p->hp.tile_form ? p->hp.tile_points
+                        : p->hp.expand_mode != sho::kExpandRows
                             ? p->hp.block_points
                             : p->hp.rows_touched * (int64_t)p->hp.grid.n[0];
   info->expand_scratch_doubles = p->hp.u2_doubles;

@@ -283,6 +283,7 @@ struct HostPlan {
   std::vector<std::array<int8_t, 3>> timages;  // Bloch plans: periodic image of
                                                // every entry (as in EntryRec)
   std::vector<uint16_t> tcover;         // [tile][row]: bit x where a support is
+  int64_t tile_points = 0;              // points that the tiles move
   int32_t proj_form = 0;                // kProjectItems or kProjectBlocks
   bool plane_form = false;              // the item form runs by planes
   bool plane_rule = false;              // so it does with the default schedule
@@ -440,7 +441,7 @@ inline int plane_waves(const HostPlan &P) {
 void build_planes(HostPlan *P);
 
 // Blocks and entries of the tile form of the expansion (needs build_rows);
-// sets tile_form and block_points.  Nothing is built for plans that cannot
+// sets tile_form and tile_points.  Nothing is built for plans that cannot
 // take the form.
 void build_tiles(HostPlan *P);
 

@@ -1012,15 +1012,12 @@ void build_tiles(HostPlan *P) {
   }
   // blocks of planes z = k mod 8 go to workgroups g = k mod 8 (XCD k)
   std::vector<BlockRec> cls[kXcds];
-  P->block_points = 0;
   for (int32_t b = 0; b < nz * nyb * nxb; ++b) {
     const int32_t e0 = begin[(size_t)b * kNu], n = begin[(size_t)(b + 1) * kNu] - e0;
     if (!n) continue;
     const int32_t z = b / (nyb * nxb);
     const BlockRec B{z, b / nxb % nyb * kTileRows, b % nxb * kTileX, e0, n, 0};
     cls[z % kXcds].push_back(B);
-    P->block_points += (int64_t)(std::min(B.y0 + kTileRows, ny) - B.y0) *
-                       (std::min(B.x0 + kTileX, nx) - B.x0);
   }
   size_t most = 0;
   for (const auto &c : cls) most = std::max(most, c.size());
@@ -1034,6 +1031,8 @@ void build_tiles(HostPlan *P) {
     if (B.nentries >= 0)
       std::copy_n(cover.begin() + b * kTileRows, kTileRows, P->tcover.begin() + i * kTileRows);
   }
+  P->tile_points = 0;
+  for (uint16_t m : P->tcover) P->tile_points += __builtin_popcount(m);
   P->tile_form = true;
 }
 

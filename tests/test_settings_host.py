@@ -73,7 +73,7 @@ def test_band_tile_leaves_deterministic_plans_their_form():
 def _state(p):
     info = _info(p)
     return (p.forms(), p.schedule(), p.expand_form(), p.expand_tile(), info["expand_blocks"],
-            info["expand_entries"])
+            info["expand_entries"], info["expand_points"])
 
 
 @pytest.mark.parametrize("kind", sorted(KINDS))
@@ -128,4 +128,21 @@ def test_project_blocks_and_back():
     assert p.forms()[0] == bd.PROJECT_BLOCKS
     p.set_project(bd.PROJECT_ITEMS)
     assert _state(p) == fresh
+    p.close()
+
+
+@pytest.mark.parametrize("kind", ["f64", "det", "f32", "bloch"])
+def test_expand_points_of_tiles_and_blocks(kind):
+    """Tiles move the points that a support holds, blocks whole blocks, whatever
+    ran before."""
+    p = _plan(KINDS[kind])
+    first = _info(p)
+    assert p.forms()[2] == bd.FORM_TILES
+    assert first["expand_points"] == first["union_points"]
+    mode = p.expand_form()[0]
+    p.set_expand(mode, *((0, 16) if kind == "det" else (2, 8)))
+    assert p.forms()[2] == mode
+    assert _info(p)["expand_points"] >= first["union_points"]
+    p.set_expand(mode)
+    assert _info(p)["expand_points"] == first["union_points"]
     p.close()
