@@ -825,8 +825,11 @@ bool uses_planes(const sho_plan_s *p) {
   return p->hp.plane_form && p->hp.proj_form == sho::kProjectItems;
 }
 
-// How it runs with the plan's scratch at hand.
+// How it runs with the plan's scratch at hand, and without.
 Items with_scratch(const sho_plan_s *p) { return uses_planes(p) ? Items::kPlanes : Items::kWork; }
+Items without_scratch(const sho_plan_s *p) {
+  return uses_planes(p) && (p->hp.flags & SHO_FLAG_DETERMINISTIC) ? Items::kAtoms : Items::kWork;
+}
 
 // run_project with the plane sums of the block or plane form in the plan's
 // own scratch, ordered against the scratch's other users (the other forms use
@@ -838,7 +841,7 @@ Items with_scratch(const sho_plan_s *p) { return uses_planes(p) ? Items::kPlanes
 hipError_t run_project_own(sho_plan_s *p, const void *psi, void *c, hipStream_t s, bool prof) {
   Items how = with_scratch(p);
   if (how == Items::kPlanes && (capturing(s) || ensure_u2(p) != SHO_OK))
-    how = (p->hp.flags & SHO_FLAG_DETERMINISTIC) ? Items::kAtoms : Items::kWork;
+    how = without_scratch(p);
   if (how != Items::kPlanes && p->hp.proj_form != sho::kProjectBlocks)
     return run_project(p, psi, c, s, prof, how);
   hipError_t e = scratch_acquire(p, s);
@@ -1752,8 +1755,10 @@ sho_status sho_plan_tune(sho_plan_t p, const void *psi, void *c, int32_t reps,
     return fail(SHO_E_INVALID, "stored and per-atom plans have a fixed schedule");
   const bool blocks_ok =
       !(p->hp.flags & SHO_FLAG_DETERMINISTIC) && !p->fp32 && !p->bloch;
-  const bool planes0 = uses_planes(p);
-  if ((blocks_ok || planes0) && (st = ensure_u2(p)) != SHO_OK) return st;
+  if (blocks_ok && (st = ensure_u2(p)) != SHO_OK) return st;
+  // (the plane form gives way without scratch, here as in a call)
+  const bool scratch = !uses_planes(p) || ensure_u2(p) == SHO_OK;
+  const bool planes0 = uses_planes(p) && scratch;
   hipStream_t s = (hipStream_t)stream;
   struct Cand {
     int32_t sched, tbs;
@@ -1769,11 +1774,13 @@ sho_status sho_plan_tune(sho_plan_t p, const void *psi, void *c, int32_t reps,
   }
   const Cand before{p->hp.sched, tb0, p->hp.target_points};
   const int32_t form0 = p->hp.proj_form;
+  const int32_t pblk0_rows = p->hp.pblk.rows, pblk0_x = p->hp.pblk.x,
+                pblk0_tbs = p->hp.pblk_tb_shift;
   hipEvent_t ea = nullptr, eb = nullptr;
   hipError_t e = hipEventCreate(&ea);
   if (e == hipSuccess) e = hipEventCreate(&eb);
   auto time_current = [&](double *ms) -> hipError_t {
-    const Items how = with_scratch(p);
+    const Items how = scratch ? with_scratch(p) : without_scratch(p);
     hipError_t e1 = run_project(p, psi, c, s, false, how);  // warm-up
     if (e1 == hipSuccess) e1 = hipEventRecord(ea, s);
     for (int r = 0; r < reps && e1 == hipSuccess; ++r)
@@ -1845,8 +1852,20 @@ sho_status sho_plan_tune(sho_plan_t p, const void *psi, void *c, int32_t reps,
   }
   if (ea) (void)hipEventDestroy(ea);
   if (eb) (void)hipEventDestroy(eb);
-  if (e != hipSuccess) return hip_fail(e, "tuning");
-  if ((e = hipStreamSynchronize(s)) != hipSuccess) return hip_fail(e, "tuning");
+  if (e == hipSuccess) e = hipStreamSynchronize(s);
+  if (e != hipSuccess) {
+    // the plan as it was
+    sho::build_work(&p->hp, before.tbs, before.target, before.sched);
+    (void)upload_schedule(p);
+    if (form0 == sho::kProjectBlocks) {
+      sho::build_block_set(&p->hp, pblk0_rows, pblk0_x, &p->hp.pblk);
+      p->hp.pblk_tb_shift = pblk0_tbs;
+      (void)upload_pblocks(p);
+    }
+    p->hp.proj_form = form0;
+    p->hp.plane_form = plane_form0;
+    return hip_fail(e, "tuning");
+  }
   sho::build_work(&p->hp, pick.tbs, pick.target, pick.sched);
   if ((e = upload_schedule(p)) != hipSuccess) return hip_fail(e, "schedule upload");
   p->hp.plane_form = keep_planes;

@@ -87,3 +87,51 @@ def test_results_through_a_round_trip_of_settings(flags):
     if plan.forms()[2] == bd.FORM_TILES:  # (blocks add with atomics)
         assert torch.equal(e0, e1)
     plan.close()
+
+
+@pytest.mark.parametrize("flags", ["f32", "det"])
+def test_projection_and_tuner_without_room_for_the_scratch(flags):
+    """A plan whose plane sums do not fit what is left of the card (80 atoms of
+    cut-off 10 and 200 planes, 320 values per point: 2.7 GB of 2.1) projects
+    without them, and the tuner does not refuse it.  The bands repeat 32 of a
+    small plan.  Both sum at most 3200 terms, so they agree within 2 * 3300 roundings of h^3 sum |psi P|,
+    which is at most the norm of psi (P has norm 1)."""
+    bd = _bd()
+    f32 = flags == "f32"
+    fl = bd.FLAG_FP32 if f32 else bd.FLAG_DETERMINISTIC
+    nbands = 640 if f32 else 320
+    rng = np.random.default_rng(5)
+    pos = rng.uniform(0.2, 0.6, size=(80, 3))
+    pos[:, 2] = rng.uniform(18.0, 22.0, size=80)
+    geo = dict(n=(4, 4, 200), h=0.2, periodic=(False,) * 3, pos=pos, sigma=np.full(80, 6.0),
+               numax=np.full(80, 10, dtype=np.int32), rbox=np.full(80, 30.0), flags=fl)
+    dt = torch.float32 if f32 else torch.float64
+    small = torch.from_numpy(rng.standard_normal((3200, 32))).to("cuda", dt)
+    plan = bd.Plan(nbands=32, **geo)
+    ref = plan.project(small.reshape(-1)).reshape(-1, 1, 32).clone()
+    plan.close()
+    torch.cuda.empty_cache()
+    left = 2 << 30
+    taken = torch.empty(torch.cuda.mem_get_info()[0] - left, dtype=torch.uint8, device="cuda")
+    plan = bd.Plan(nbands=nbands, **geo)
+    assert plan.forms()[0] == bd.FORM_PLANES
+    assert plan.info["expand_scratch_doubles"] * 8 > 1.2 * left
+    assert torch.cuda.mem_get_info()[0] > left // 2  # no room was found for it
+    psi = small.repeat(1, nbands // 32).reshape(-1)
+    c = torch.full((plan.coeff_doubles,), float("nan"), dtype=dt, device="cuda")
+    norm = float((0.2 ** 3 * (small.double() ** 2).sum(dim=0)).max()) ** 0.5
+    tol = 2 * 3300 * (2.0 ** -24 if f32 else 2.0 ** -53) * norm
+    for step in range(2):
+        plan.project(psi, c)
+        torch.cuda.synchronize()
+        for rows in c.reshape(-1, nbands // 32, 32).split(1024):
+            at = rows.data_ptr() - c.data_ptr()
+            r0 = at // (c.element_size() * nbands)
+            assert float((rows - ref[r0:r0 + rows.shape[0]]).abs().max()) <= tol
+        if step == 0:
+            r = plan.tune(psi, c, reps=1)
+            assert r["candidates"] >= 2 and r["project_form"] == bd.PROJECT_ITEMS
+            c.fill_(float("nan"))
+    plan.close()
+    del taken
+    torch.cuda.empty_cache()
