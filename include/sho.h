@@ -546,8 +546,8 @@ typedef struct sho_tune_expand_result {
  * per candidate) under the block form with every band tile from 8 to the
  * one covering nbands and a few block shapes per tile (the default, half the
  * rows, half the width, twice the rows at half the width), and the row form
- * (FP64 plans of real bands), reps launches each after one warm-up, on
- * stream, and keeps the fastest.  Synchronous.  Refused (SHO_E_INVALID) on
+ * (FP64 plans of real bands), and as tiles, reps launches each after one
+ * warm-up, on stream, and keeps the fastest.  Synchronous.  Refused (SHO_E_INVALID) on
  * stored, per-atom and deterministic plans.  result may be NULL.
  */
 sho_status sho_plan_tune_expand(sho_plan_t plan, const void *c, void *psi, int32_t reps,
@@ -567,7 +567,8 @@ typedef struct sho_tune_result {
  * Autotuner: times the projection of psi into c (both device buffers of the
  * plan's sizes; c is overwritten) under every schedule (with and without
  * SHO_SCHED_XCD) x work item size
- * {4096, 8192, 16384, 32768} x band tile {current, half}, and (FP64 plans of
+ * {4096, 8192, 16384, 32768} x band tile {current, half}, plane by plane (with
+ * the default schedule, where the plan has room for the scratch), and (FP64 plans of
  * real bands, not deterministic) the block form of the projection with band
  * tiles 8..32 and blocks 16..64 points wide, reps launches each after one
  * warm-up, on stream, and keeps the fastest (the item schedule is kept for

@@ -1681,6 +1681,14 @@ sho_status sho_plan_tune_expand(sho_plan_t p, const void *c, void *psi, int32_t 
     p->hp.expand_tbe_shift = keep;
   }
   if (!p->fp32 && !p->bloch) cands.push_back({sho::kExpandRows, -1, 0, 0, false});
+  if (!p->hp.tblocks.empty() && !p->hp.tile_form) {
+    const int32_t keep = p->hp.expand_tbe_shift;
+    p->hp.expand_tbe_shift = -1;
+    int32_t R = 0, X = 0;
+    sho::default_block_shape(p->hp, &R, &X);
+    p->hp.expand_tbe_shift = keep;
+    cands.push_back({sho::kExpandBlocks, -1, R, X, true});
+  }
   hipEvent_t ea = nullptr, eb = nullptr;
   hipError_t e = hipEventCreate(&ea);
   if (e == hipSuccess) e = hipEventCreate(&eb);
@@ -1757,7 +1765,7 @@ sho_status sho_plan_tune(sho_plan_t p, const void *psi, void *c, int32_t reps,
       !(p->hp.flags & SHO_FLAG_DETERMINISTIC) && !p->fp32 && !p->bloch;
   if (blocks_ok && (st = ensure_u2(p)) != SHO_OK) return st;
   // (the plane form gives way without scratch, here as in a call)
-  const bool scratch = !uses_planes(p) || ensure_u2(p) == SHO_OK;
+  const bool scratch = p->hp.punits.empty() || ensure_u2(p) == SHO_OK;
   const bool planes0 = uses_planes(p) && scratch;
   hipStream_t s = (hipStream_t)stream;
   struct Cand {
@@ -1819,6 +1827,23 @@ sho_status sho_plan_tune(sho_plan_t p, const void *psi, void *c, int32_t reps,
       best = ms;
       pick = cd;
       keep_planes = false;
+    }
+  }
+  // the plane form, which goes with the default schedule
+  if (e == hipSuccess && !planes0 && scratch && !p->hp.punits.empty()) {
+    const Cand planes{p->hp.sched0, p->hp.tb_shift0, p->hp.target_points0};
+    e = hipStreamSynchronize(s);
+    sho::build_work(&p->hp, planes.tbs, planes.target, planes.sched);
+    if (e == hipSuccess) e = upload_schedule(p);
+    p->hp.plane_form = true;
+    double ms = 0.0;
+    if (e == hipSuccess) e = time_current(&ms);
+    p->hp.plane_form = false;
+    ++tried;
+    if (e == hipSuccess && ms < best) {
+      best = ms;
+      pick = planes;
+      keep_planes = true;
     }
   }
   // block form: band tile x block width (rows: as many as the tile holds)
