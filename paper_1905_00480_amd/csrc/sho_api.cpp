@@ -1719,7 +1719,7 @@ sho_status sho_plan_tune_expand(sho_plan_t p, const void *c, void *psi, int32_t 
     if (cd.tiles) {
       p->hp.blk_rows = cd.R;
       p->hp.blk_x = cd.X;
-    } else if (cd.mode == sho::kExpandBlocks) {
+    } else if (cd.mode != sho::kExpandRows) {  // (the owner form: its strips)
       sho::build_blocks(&p->hp, cd.R, cd.X);
       e1 = upload_blocks(p);
     }
@@ -1738,7 +1738,10 @@ sho_status sho_plan_tune_expand(sho_plan_t p, const void *c, void *psi, int32_t 
   }
   if (ea) (void)hipEventDestroy(ea);
   if (eb) (void)hipEventDestroy(eb);
-  if (e != hipSuccess) return hip_fail(e, "tuning");
+  if (e != hipSuccess) {
+    (void)apply(before);
+    return hip_fail(e, "tuning");
+  }
   if ((e = apply(pick)) != hipSuccess) return hip_fail(e, "expansion form upload");
   p->sched_version++;
   if (result) {

@@ -165,3 +165,22 @@ def test_tuners_come_back_to_the_default_forms():
         _check(plan.expand(d_w, d_psi.clone()),
                *oracle.expand(*s.geometry(), w, psi, with_abs=True), "tuned")
     plan.close()
+
+
+@pytest.mark.parametrize("nbands", [1, 3, 7, 20])
+def test_expansion_tuner_from_the_owner_form(nbands):
+    """Where the owner form is the fastest, it is left with its own strips (and
+    not the last block shape that was timed)."""
+    bd = _bd()
+    s = wl.make_system("own", (40, 36, 33), 0.2, (True, False, True), 9, 0.6, 4, nbands, 77)
+    psi, w = wl.psi_for(s), wl.coeffs_for(s)
+    ref = oracle.expand(*s.geometry(), w, psi, with_abs=True)
+    for width in (16, 32):
+        plan = bd.Plan.from_system(s)
+        plan.set_expand(bd.EXPAND_OWNER, 0, width)
+        own = plan.expand_form()
+        plan.tune_expand(_dev(w), _dev(psi), reps=3)
+        if plan.forms()[2] == bd.EXPAND_OWNER:
+            assert plan.expand_form() == own
+        _check(plan.expand(_dev(w), _dev(psi)), *ref, "after tuning from %s" % (own,))
+        plan.close()
