@@ -196,17 +196,23 @@ constexpr int slot_bytes(int numax) {
 // the copies of the next entries would not overlap this one.  The load has no
 // register to write; the kernel waits for vmcnt(0) and a barrier before the
 // slot is read.
+// (The compiler says of every copy that m0 is a register it keeps for itself; it
+// writes m0 in front of each instruction that reads it, and none else does here.)
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
 template <int BYTES>
 __device__ inline void to_lds(const char *src, uint32_t off, uint32_t dst) {
   if constexpr (BYTES == 16)
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(dst),
                  "v"(off), "s"(src)
-                 : "memory");
+                 : "memory", "m0");
   else
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" ::"s"(dst),
                  "v"(off), "s"(src)
-                 : "memory");
+                 : "memory", "m0");
 }
+
+#pragma clang diagnostic pop
 
 // A lane's place in the copies of partials: its byte offset from the first
 // pair of a 64-lane chunk, and that pair's number in the chunk.
@@ -282,19 +288,42 @@ __device__ inline void stage(const TileArgs &E, const TileHead &en, const T *u2,
 
 // a += (phi of lane K of the own 16 lanes) * u: the vector FMA reads the table
 // value across lanes, at the rate of a plain one.  (Written out because the
-// compiler keeps the broadcast as an instruction of its own.  phi and u must
-// not come straight from a vector or matrix instruction: settle them first.)
-template <int K>
+// compiler keeps the broadcast as an instruction of its own.)  A DPP read takes
+// two wait states behind a vector instruction that writes the register, which the
+// compiler does not see the need of here: a point's first one brings them (and
+// volatile keeps it first).  u must not come straight from a matrix instruction:
+// settle it.
+#define SHO_FMA "v_fmac_f64_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf"
+template <int K, bool kFirst>
 __device__ inline void fma_from(double &a, double phi, double u) {
-  asm("v_fmac_f64_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf"
-      : "+v"(a)
-      : "v"(phi), "v"(u), "n"(K));
+  if constexpr (kFirst)
+    asm volatile("s_nop 1\n\t" SHO_FMA : "+v"(a) : "v"(phi), "v"(u), "n"(K));
+  else
+    asm volatile(SHO_FMA : "+v"(a) : "v"(phi), "v"(u), "n"(K));
 }
+#undef SHO_FMA
 template <int K, int NF, int NB, int N = 0>
 __device__ inline void add_point(double (&a)[NB], double phi, const double (&U)[NF][NB]) {
-#pragma unroll
-  for (int h = 0; h < NB; ++h) fma_from<K + N>(a[h], phi, U[N][h]);
+  fma_from<K + N, N == 0>(a[0], phi, U[N][0]);
+  if constexpr (NB == 2) fma_from<K + N, false>(a[1], phi, U[N][1]);
   if constexpr (N + 1 < NF) add_point<K, NF, NB, N + 1>(a, phi, U);
+}
+
+// The U, written by matrix instructions, may be read by others from here on (the
+// last takes up to 18 wait states, which the compiler does not see the need of
+// before an asm).  They pass through on both sides of the wait, so that nothing
+// that writes them moves down over it and nothing that reads them up.
+template <int NF, int NB>
+__device__ inline void settle(double (&U)[NF][NB]) {
+#pragma unroll
+  for (int n = 0; n < NF; ++n)
+#pragma unroll
+    for (int h = 0; h < NB; ++h) asm volatile("" : "+v"(U[n][h]));
+  asm volatile("s_nop 15\n\ts_nop 3" ::: "memory");
+#pragma unroll
+  for (int n = 0; n < NF; ++n)
+#pragma unroll
+    for (int h = 0; h < NB; ++h) asm volatile("" : "+v"(U[n][h]));
 }
 
 // Adds one entry to the wave's 4 rows (4 w + quarter) x 32 points.  range: the
@@ -337,7 +366,7 @@ __device__ inline void add_entry(const TileArgs &E, uint32_t range, uint32_t ste
       const bool there = m == 3 || q <= m;
 #pragma unroll
       for (int h = 0; h < NB; ++h)
-        U[nx][h] = mfma4(ay[g], there ? (double)u.v[h] : 0.0, U[nx][h]);
+        U[nx][h] = mfma4(ay[g], (double)(there ? u.v[h] : T(0)), U[nx][h]);
     }
     p += NF - nx;
   }
@@ -368,11 +397,7 @@ __device__ inline void add_entry(const TileArgs &E, uint32_t range, uint32_t ste
   double ph[2][kRegs];
 #pragma unroll
   for (int k = 0; k < kRegs; ++k) ph[0][k] = xt[k * kPer * nfp];
-#pragma unroll
-  for (int n = 0; n < NF; ++n)
-#pragma unroll
-    for (int h = 0; h < NB; ++h) asm volatile("" : "+v"(U[n][h]));
-  asm volatile("s_nop 15\n\ts_nop 3" ::: "memory");  // the last matrix result is in place
+  settle(U);
 #pragma unroll
   for (int t = 0; t < kTileX / kStep; ++t) {
     if (t + 1 < kTileX / kStep) {
