@@ -631,6 +631,8 @@ void build_planes(HostPlan *P) {
   const bool many = bands <= 8 && (P->nu_max <= 3 ? units >= 640 * bands
                                                   : P->nu_max <= 5 && bands <= 4 &&
                                                         units >= 8192);
+  // (a launch takes fewer than 2^32 threads along x)
+  if ((int64_t)P->punits.size() * plane_waves(*P) * 64 >= (int64_t)1 << 32) return;
   P->plane_form = !((units <= 64 || bands <= 8) && largest <= 4096) && !many &&
                   !(f32 && P->support_points < 4 * P->union_points);
   P->plane_rule = P->plane_form;
@@ -1024,6 +1026,16 @@ void build_tiles(HostPlan *P) {
   const BlockRec pad{0, 0, 0, 0, -1, 0};
   for (size_t i = 0; i < most; ++i)
     for (const auto &c : cls) P->tblocks.push_back(i < c.size() ? c[i] : pad);
+  // a launch takes fewer than 2^32 threads along x, where a tile's band groups
+  // are (four waves each)
+  const int64_t reals = (int64_t)P->nbands * ((P->flags & SHO_FLAG_FP32) ? 2 : 1);
+  const int64_t groups = reals > 16 ? (reals + 31) / 32 : 1;
+  if ((int64_t)P->tblocks.size() * groups * 256 >= (int64_t)1 << 32) {
+    P->tblocks.clear();
+    P->tentries.clear();
+    P->timages.clear();
+    return;
+  }
   P->tcover.assign(P->tblocks.size() * kTileRows, 0);
   for (size_t i = 0; i < P->tblocks.size(); ++i) {
     const BlockRec &B = P->tblocks[i];

@@ -146,3 +146,14 @@ def test_expand_points_of_tiles_and_blocks(kind):
     p.set_expand(mode)
     assert _info(p)["expand_points"] == first["union_points"]
     p.close()
+
+
+def test_launches_too_large_for_tiles_stay_with_blocks():
+    """64 planes of a 4 x 4 column are 64 tiles; a launch of 64 x 2^18 band groups
+    of 256 threads would be 2^32."""
+    for nbands, form in ((1 << 22, bd.FORM_TILES), (1 << 23, bd.EXPAND_BLOCKS)):
+        p = bd.Plan((4, 4, 64), 0.3, (False,) * 3, [[0.5, 0.5, 9.5]], [1.0], [1], nbands,
+                    rbox=[12.0], flags=bd.FLAG_HOST_ONLY)
+        assert p.forms()[2] == form
+        assert _info(p)["expand_blocks"] > 0
+        p.close()
