@@ -178,8 +178,7 @@ struct TileHead {
   int32_t tab_x;       // table double of memory x = x0 (as in EntryRec)
   int32_t tab_y;       // table double of block row 0
   int16_t nu, nfp;
-  int8_t x_lo, x_hi;   // x rows of the table that exist, relative to x0
-  int8_t y_lo, y_hi;   // y rows that exist, relative to y0
+  int32_t pad;
 };
 // A wave's rows of an entry, 4 w + r for r = 0..3: 16 bits each, row 2 i in
 // the low half of d[i]: x begin | x end << 6 relative to x0 (0: no run); and
@@ -396,8 +395,9 @@ void build_rows(HostPlan *P);
 constexpr int64_t kTabPad = 32 * 16;
 
 // Limits of the plane form: bytes of a memory plane of psi and of an atom's
-// widest line (32-bit offsets, bit 31 marks lanes without a value), x table rows of an atom in LDS (at most
-// 12 functions of 8 bytes each per row) and bundles of a unit (72 bytes each).
+// widest line (32-bit offsets, bit 31 marks lanes without a value), x table rows
+// of an atom in LDS (at most 12 functions of 8 bytes each per row) and bundles
+// of a unit (48 bytes each).
 constexpr int64_t kPlaneMaxBytes = (int64_t)1 << 30;
 constexpr int32_t kPlaneMaxRows = 256;
 constexpr int32_t kPlaneMaxBundles = 256;
@@ -406,18 +406,6 @@ constexpr int32_t kPlaneMaxBundles = 256;
 // two where one wave of 16 would not hold all bands.
 inline int plane_bands(const HostPlan &P) {
   return P.nbands * ((P.flags & SHO_FLAG_FP32) ? 2 : 1) > 16 ? 2 : 1;
-}
-
-// log2 of the band groups (16 bands) that run side by side on an XCD: as many
-// as keep a memory plane of them within 2 MB (half the L2), at most 8.
-inline int plane_group_shift(const HostPlan &P) {
-  const bool f32 = (P.flags & SHO_FLAG_FP32) != 0;
-  const int bands = 16 * plane_bands(P);
-  const int64_t plane = (int64_t)P.grid.n[0] * P.grid.n[1] * bands * (f32 ? 4 : 8);
-  const int groups = (P.nbands * (f32 ? 2 : 1) + bands - 1) / bands;
-  int s = 0;
-  while (s < 3 && (1 << s) < groups && (plane << (s + 1)) <= (2 << 20)) ++s;
-  return s;
 }
 
 // Waves per unit of the plane form.  Few units: four, for the parallelism

@@ -969,10 +969,6 @@ void build_tiles(HostPlan *P) {
             E.tab_y = tab_y;
             E.nu = (int16_t)A.nu;
             E.nfp = (int16_t)A.tab_nfp;
-            E.x_lo = (int8_t)std::max(0, -jx0);
-            E.x_hi = (int8_t)std::min(kTileX, A.mx - jx0);
-            E.y_lo = (int8_t)std::max(0, -jy0);
-            E.y_hi = (int8_t)std::min(kTileRows, A.my - jy0);
             if (bloch) {
               const int64_t img[3] = {((int64_t)A.ix0 + L.jx0 - L.x0m) / nx,
                                       ((int64_t)A.iy0 + L.jy - y) / ny,

@@ -1,14 +1,14 @@
-// sho_planes.hip -- the plane form of the projection: one wave per
-// (atom plane, 16 bands), the x and y passes on FP64 matrix cores, plane sums
-// to memory, then one z pass over all atoms.
+// sho_planes.hip -- the plane form of the projection: one, two or four waves per
+// (atom plane, 16 or 32 bands), the x and y passes on FP64 matrix cores, plane
+// sums to memory, then one z pass over all atoms.
 //
 // What bounds the projection is the re-reading of psi: overlapping supports
 // read every covered value once per atom (2.3 times at 128^3 / 512 atoms /
 // cut-off 5, 18 times at 160^3 / 2048 atoms / cut-offs 3..9).  The item form
 // (one workgroup per atom) reads from behind the L2 at 5.6 TB/s.  Here the
 // unit of work is an atom plane, and the units are launched plane by plane of
-// the grid, one plane per XCD at a time and 16 bands at a time: a 160^2 plane
-// of 16 bands is 3.3 MB, so the units resident on an XCD meet in its 4 MB L2
+// the grid, one plane per XCD at a time and one band group at a time: a 160^2
+// plane of 16 bands is 3.3 MB, so the units resident on an XCD meet in its 4 MB L2
 // (measured read rates: 19 TB/s from L2, 7 from the memory-side cache, 6 from
 // HBM).  Sixteen bands are also one 128-byte line per grid point.
 //

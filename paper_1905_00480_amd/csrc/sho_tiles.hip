@@ -252,7 +252,7 @@ __device__ inline void stage(const TileArgs &E, const TileHead &en, const T *u2,
   const char *xs = tab + (int64_t)en.tab_x * 8;
   const char *ys = tab + (int64_t)en.tab_y * 8;
   const uint32_t off16 = (uint32_t)lane * 16;
-  // x rows: 2 or 4 chunks, y rows: 1 or 2
+  // x rows and y rows: one or two chunks of 1024 bytes each
   if (en.nfp == 8) {
     if (w == 0)
       to_lds<16>(xs, off16, slot);
@@ -326,7 +326,7 @@ __device__ inline void settle(double (&U)[NF][NB]) {
     for (int h = 0; h < NB; ++h) asm volatile("" : "+v"(U[n][h]));
 }
 
-// Adds one entry to the wave's 4 rows (4 w + quarter) x 32 points.  range: the
+// Adds one entry to the wave's 4 rows (4 w + quarter) x 16 points.  range: the
 // run of the lane's row within the tile, begin | end << 6; steps: bit t where
 // points 2 t, 2 t + 1 are in a run of any of the four.
 template <typename T, int NU, int NUMAX, int NB>
