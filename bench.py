@@ -13,12 +13,15 @@ functions), 32 real FP64 bands psi ~ N(0,1) (synthetic, seeded).
 Metric: projected gridpoint*bands per second = sum_a |S_a| * B per step / time.
 
 Kernels of a step and their algorithmic HBM bytes per launch:
-  project        box reads sum_a |S_a| B 8 + coefficient writes
+  project        read of every grid value some support covers (union points
+                 * B * 8; overlapping supports meet in L2) + coefficient writes
   expand_z       coefficient reads + plane-partial writes (U2, z pass)
   expand_xy      read + write of every grid value some support covers
                  (2 * union points * B * 8) + plane-partial reads (y and x
-                 passes; the blocks it moves also hold a few uncovered values)
-The roofline object is the dominant (longest) kernel's bytes over its mean
+                 passes)
+The per-atom figures beside them count a value once per support that holds it,
+as the paper does: more than HBM moves, so no fraction of its peak is taken of
+them.  The roofline object is the dominant (longest) kernel's bytes over its mean
 duration, both measured in this run with HIP events that the library records
 around its own launches on the launch stream, against 8 TB/s.  `traffic` is
 the dominant kernel's HBM bytes per launch from rocprofv3 FETCH_SIZE /
@@ -454,10 +457,8 @@ def bloch_step(bd, wl, args, ms_fp64):
 
 def deterministic_step(bd, wl, args, ms_default):
     """The scale workload with SHO_FLAG_DETERMINISTIC (every sum in an order
-    fixed by the plan: per-wave coefficient tiles added in wave order, one
-    work item per atom, the owner form of the expansion); step = projection
-    + expansion, FP64, default schedule.  Also checks that two steps on the
-    same inputs give identical bits."""
+    fixed by the plan); step = projection + expansion, FP64, default settings.
+    Also checks that two steps on the same inputs give identical bits."""
     import torch
     s = wl.scale()
     psi = torch.from_numpy(wl.psi_for(s)).cuda()
@@ -494,9 +495,9 @@ def deterministic_step(bd, wl, args, ms_default):
 
 def by_cutoff(bd, wl, reps=10):
     """The batching workload's projection on subsets of its atoms by cut-off
-    (each subset a plan of its own over the same psi, default schedule,
-    64-band tiles): mean ms per launch over `reps` launches and the per-atom
-    box bytes per second.  Shows which cut-offs stream below the rest."""
+    (each subset a plan of its own over the same psi, default settings): mean
+    ms per launch over `reps` launches and the per-atom box bytes per second.
+    Shows which cut-offs stream below the rest."""
     import torch
     s = wl.batching()
     psi = torch.from_numpy(wl.psi_for(s)).cuda()
@@ -507,8 +508,6 @@ def by_cutoff(bd, wl, reps=10):
     for name, rng in subsets:
         sub = s if rng is None else s.subset(np.nonzero((nus >= rng[0]) & (nus <= rng[1]))[0])
         plan = bd.Plan.from_system(sub)
-        sched = plan.schedule()
-        plan.set_schedule(sched[0], 64, sched[2])
         c = torch.empty(plan.coeff_doubles, dtype=torch.float64, device="cuda")
         for _ in range(3):
             plan.project(psi, c)
@@ -520,7 +519,7 @@ def by_cutoff(bd, wl, reps=10):
         ms = plan.profile_read()["project"][1]
         plan.profile(False)
         gbytes = plan.support_points * s.nbands * 8 / 1e9
-        rows.append({"nu": name, "atoms": int(sub.natoms), "schedule": list(plan.schedule()),
+        rows.append({"nu": name, "atoms": int(sub.natoms), "forms": list(plan.forms()),
                      "support_points": int(plan.support_points), "project_ms": round(ms, 4),
                      "per_atom_box_TB/s": round(gbytes / ms, 3)})
         _log("cut-offs %s: %.3f ms" % (name, ms))
@@ -817,28 +816,27 @@ def main():
 
     coeff_bytes = plan.coeff_doubles * 8
     u2_bytes = info["expand_scratch_doubles"] * 8
-    # per-atom box accounting (every atom's support counted once per atom,
-    # as the paper counts each grid value once per projection it enters)
+    # every covered value once, and per-atom box accounting (every atom's
+    # support counted once per atom, as the paper counts each grid value once
+    # per projection it enters)
+    once = info["union_points"] * B * 8
     kbytes = {
-        "project": S * B * 8 + coeff_bytes,
-        "expand_z": coeff_bytes + u2_bytes,
-        "expand_xy": 2 * S * B * 8 + u2_bytes,
+        "project": (once + coeff_bytes, S * B * 8 + coeff_bytes),
+        "expand_z": (coeff_bytes + u2_bytes,) * 2,
+        "expand_xy": (2 * once + u2_bytes, 2 * S * B * 8 + u2_bytes),
     }
     kernels = {}
-    for k, nbytes in kbytes.items():
+    for k, (nbytes, per_atom) in kbytes.items():
         n, ms = prof[k]
-        gbs = nbytes / (ms * 1e-3) / 1e9 if ms > 0 else None
+        rate = (lambda b: b / (ms * 1e-3) / 1e9 if b and ms > 0 else None)
         hbm = measured_traffic(k)
-        kernels[k] = {"launches": n, "ms": ms, "bytes_per_atom_accounting": nbytes,
-                      "GB/s": gbs, "frac_per_atom": gbs / HBM_PEAK_GBS if gbs else None,
+        kernels[k] = {"launches": n, "ms": ms, "bytes": nbytes, "GB/s": rate(nbytes),
+                      "frac": rate(nbytes) / HBM_PEAK_GBS if ms > 0 else None,
+                      "bytes_per_atom_accounting": per_atom, "per_atom_GB/s": rate(per_atom),
                       "hbm_bytes_counters": hbm,
-                      "frac_counters": (hbm / (ms * 1e-3) / 1e9 / HBM_PEAK_GBS
-                                        if hbm and ms > 0 else None)}
-    # the expansion writes each covered value once: its unique bytes
-    kernels["expand_xy"]["bytes_unique_points"] = (2 * info["union_points"] * B * 8
-                                                   + u2_bytes)
+                      "frac_counters": rate(hbm) / HBM_PEAK_GBS if rate(hbm) else None}
     dom = max(kernels, key=lambda k: kernels[k]["ms"])
-    d = kernels["project"]
+    d = kernels[dom]
     ceil = ceilings()
     # unique-psi floor of the step: every covered value read once by the
     # projection and read + written once by the expansion, or the x-pass flops
@@ -870,15 +868,13 @@ def main():
                                "step = projection + expansion",
                    "bands": B, "support_points": S,
                    "union_points": info["union_points"], "grid": list(s.n)},
-        "roofline": {"bound": "hbm", "kernel": "project", "achieved": d["GB/s"],
+        "roofline": {"bound": "hbm", "kernel": dom, "achieved": d["GB/s"],
                      "peak": HBM_PEAK_GBS, "unit": "GB/s",
-                     "frac": d["frac_per_atom"], "traffic": d["hbm_bytes_counters"],
+                     "frac": d["frac"], "traffic": d["hbm_bytes_counters"],
                      "frac_counters": d["frac_counters"],
-                     "algorithmic_bytes_per_launch": d["bytes_per_atom_accounting"],
+                     "algorithmic_bytes_per_launch": d["bytes"],
                      "launch_ms": d["ms"],
-                     "frac_of_read_ceiling": d["GB/s"] / ceil["read_GB/s"],
-                     "dominant_kernel": dom,
-                     "dominant_frac_per_atom": kernels[dom]["frac_per_atom"]},
+                     "frac_of_copy_ceiling": d["GB/s"] / ceil["copy_GB/s"]},
         "ceilings": ceil,
         "unique_psi_floor_ms_per_step": floor_ms,
         "kernels": kernels,
