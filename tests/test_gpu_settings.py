@@ -185,3 +185,32 @@ def test_expansion_tuner_from_the_owner_form(nbands):
             assert plan.expand_form() == own
         _check(plan.expand(_dev(w), _dev(psi)), *ref, "after tuning from %s" % (own,))
         plan.close()
+
+
+@pytest.mark.parametrize("nu,nbands", [(nu, b) for nu in range(11) for b in (20, 33)])
+def test_named_forms_at_every_cutoff(nu, nbands):
+    """The forms that the defaults leave to explicit settings: work items in one
+    launch and one per cut-off, blocks, rows and strips."""
+    bd = _bd()
+    s = wl.make_system("named", (26, 23, 21), 0.2, (True, True, False), 4, 0.6, nu, nbands,
+                       800 + nu + nbands)
+    psi, w = wl.psi_for(s), wl.coeffs_for(s)
+    d_psi, d_w = _dev(psi), _dev(w)
+    prj = oracle.project(*s.geometry(), psi, with_abs=True)
+    exp = oracle.expand(*s.geometry(), w, psi, with_abs=True)
+    for flags in (0, bd.FLAG_DETERMINISTIC):
+        plan = bd.Plan.from_system(s, flags=flags)
+        for sched in (bd.SCHED_BY_NU, bd.SCHED_SINGLE_LPT):
+            plan.set_schedule(sched, 0, 8192)
+            assert plan.forms()[:2] == (bd.PROJECT_ITEMS, 0)
+            _check(plan.project(d_psi), *prj, "schedule %d" % sched)
+        _, rows, x = plan.expand_form()
+        named = [(bd.EXPAND_OWNER, 0, 16)]
+        if not flags:
+            named += [(bd.EXPAND_BLOCKS, max(1, rows // 2), x), (bd.EXPAND_BLOCKS, rows, x // 2),
+                      (bd.EXPAND_ROWS, 0, 0)]
+        for form in named:
+            plan.set_expand(*form)
+            assert plan.forms()[2] == form[0]
+            _check(plan.expand(d_w, d_psi.clone()), *exp, "expansion %s" % (form,))
+        plan.close()
