@@ -214,3 +214,20 @@ def test_named_forms_at_every_cutoff(nu, nbands):
             assert plan.forms()[2] == form[0]
             _check(plan.expand(d_w, d_psi.clone()), *exp, "expansion %s" % (form,))
         plan.close()
+
+
+def test_projection_tuner_on_deterministic_and_bloch_plans():
+    """As above; a deterministic plan is back at its bits."""
+    bd = _bd()
+    s = wl.small_periodic(natoms=6, nbands=32)
+    psi = wl.psi_for(s)
+    for flags, d_psi in ((bd.FLAG_DETERMINISTIC, _dev(psi)), (bd.FLAG_BLOCH, _dev(psi + 1j * psi))):
+        plan = bd.Plan.from_system(s, flags=flags)
+        forms, sc = plan.forms(), plan.schedule()
+        c0 = plan.project(d_psi).clone()
+        plan.set_schedule(bd.SCHED_SINGLE_LPT, 0, 4096)
+        assert plan.forms()[0] == bd.PROJECT_ITEMS
+        plan.tune(d_psi, torch.empty_like(c0), reps=10)
+        assert plan.forms() == forms and plan.schedule() == sc
+        assert torch.equal(plan.project(d_psi), c0)
+        plan.close()
